@@ -9,6 +9,7 @@
 // the host needs the bounds once, to size the quadrature from beta'.
 #include <cmath>
 #include <cstdio>
+#include <algorithm>
 #include <cstring>
 #include <new>
 #include <string>
@@ -180,6 +181,76 @@ int ensure_mats(chebdm_handle h, const Plan& pl, int64_t count) {
 }
 
 
+
+// Bytes of a handle's residue-plane buffer: operand sets with their row scales, then the residues
+// of a launch's products (as many as fit 256 MB, the chip's last-level cache, and at least one).
+struct RnsLayout {
+    RnsGeom geo;
+    int slots;
+    int64_t set_stride, products;
+    size_t bytes;
+};
+
+// Smallest N whose float64 products run on the int8 units.
+constexpr int64_t kRnsMinN = 1400;
+
+// slots == 0: float64 units.  The operand sets take at most 8 GB (12 sets up to N = 6600; below
+// three the products would convert operands over and over, and the float64 units stay).
+RnsLayout rns_layout(const Plan& pl) {
+    RnsLayout l{};
+    if (pl.prec != CHEBDM_FP64 || pl.n < kRnsMinN) return l;
+    l.geo = rns_geom(pl.n);
+    l.set_stride = l.geo.set_bytes + 2 * l.geo.rows * (int64_t)sizeof(double);
+    const int64_t fit = ((int64_t)8 << 30) / l.set_stride;
+    if (fit < 3) return l;
+    l.slots = (int)std::min<int64_t>(fit, 12);
+    l.products = std::max<int64_t>(1, std::min<int64_t>(kRnsGroup, ((int64_t)256 << 20) / l.geo.res_bytes));
+    l.bytes = (size_t)(l.slots * l.set_stride + l.products * l.geo.res_bytes);
+    return l;
+}
+
+// Residue planes for the call's products; without the memory for them the float64 units do them.
+int ensure_rns(chebdm_handle h, const Plan& pl) {
+    const RnsLayout l = rns_layout(pl);
+    h->rns_slots = 0;
+    if (l.slots == 0) return 0;
+    if (l.bytes > h->rns_bytes) {
+        if (h->rns) {
+            HIP_TRY(hipStreamSynchronize(h->stream));
+            HIP_TRY(hipFree(h->rns));
+            h->rns = nullptr;
+            h->rns_bytes = 0;
+        }
+        if (hipMalloc(&h->rns, l.bytes) != hipSuccess) {
+            h->rns = nullptr;
+            (void)hipGetLastError();
+            return 0;
+        }
+        h->rns_bytes = l.bytes;
+    }
+    h->rns_geo = l.geo;
+    h->rns_slots = l.slots;
+    h->rns_res_products = l.products;
+    return 0;
+}
+
+int8_t* rns_planes(chebdm_handle h, int s) {
+    return static_cast<int8_t*>(h->rns) + s * (h->rns_geo.set_bytes + 2 * h->rns_geo.rows * (int64_t)sizeof(double));
+}
+double* rns_scale(chebdm_handle h, int s) { return reinterpret_cast<double*>(rns_planes(h, s) + h->rns_geo.set_bytes); }
+
+// No slot holds a current matrix (a new call's matrices are about to be written).
+void rns_reset(chebdm_handle h) {
+    h->rns_owner.assign(h->rns_slots, nullptr);
+    h->rns_used.assign(h->rns_slots, 0);
+    h->rns_clock = 0;
+}
+
+// The matrices in [first, last) are about to be written.
+void rns_forget(chebdm_handle h, const void* first, const void* last) {
+    for (const void*& o : h->rns_owner)
+        if (o >= first && o < last) o = nullptr;
+}
 
 // matrix slot s (0-based) of the workspace
 void* slot(chebdm_handle h, const Plan& pl, int64_t s) {
@@ -388,13 +459,62 @@ struct Chain {
         }
         ++*n_gemm;
     }
+    // The products of b64 on the int8 units, in groups whose operands fit the plane slots and whose
+    // residues fit their buffer.  A matrix keeps its planes until it is written or its slot is
+    // the least recently used one, so T_k (every giant step) and the stages' shared factors are
+    // split once.
+    int flush_rns() {
+        const RnsGeom& g = h->rns_geo;
+        int8_t* res = rns_planes(h, h->rns_slots);
+        for (int i0 = 0; i0 < b64.count;) {
+            const int64_t stamp = ++h->rns_clock;
+            RnsProduct prod[kRnsGroup];
+            const double* mats[kRnsGroup];
+            int8_t* planes[kRnsGroup];
+            double* scale[kRnsGroup];
+            int nsplit = 0, np = 0;
+            auto operand = [&](const double* M) -> int {   // slot with M's planes, or -1: none free
+                int lru = -1;
+                for (int s = 0; s < h->rns_slots; ++s) {
+                    if (h->rns_owner[s] == M) {
+                        h->rns_used[s] = stamp;
+                        return s;
+                    }
+                    if (h->rns_used[s] != stamp && (lru < 0 || h->rns_used[s] < h->rns_used[lru])) lru = s;
+                }
+                if (lru < 0 || nsplit == kRnsGroup) return -1;
+                h->rns_owner[lru] = M;
+                h->rns_used[lru] = stamp;
+                mats[nsplit] = M;
+                planes[nsplit] = rns_planes(h, lru);
+                scale[nsplit++] = rns_scale(h, lru);
+                return lru;
+            };
+            while (i0 + np < b64.count && np < h->rns_res_products) {
+                const GemmDesc<double>& d = b64.d[i0 + np];
+                const int a = operand(d.A), b = a < 0 ? -1 : operand(d.B);
+                if (b < 0) break;
+                prod[np++] = RnsProduct{rns_planes(h, a), rns_planes(h, b), rns_scale(h, a), rns_scale(h, b), d.C, d.E,
+                                        static_cast<double*>(d.Out), d.ld_out, d.alpha, d.beta, d.gamma, d.delta, 0};
+            }
+            if (np == 0) return fail(CHEBDM_ERR_HIP, "no room for a product's operands");
+            if (nsplit > 0) HIP_TRY(launch_rns_split(g, pl.ld, mats, planes, scale, nsplit, h->stream));
+            HIP_TRY(launch_rns_products(g, pl.ld, prod, np, res, h->stream));
+            for (int i = 0; i < np; ++i)
+                for (const void*& o : h->rns_owner)
+                    if (o == b64.d[i0 + i].Out) o = nullptr;
+            i0 += np;
+        }
+        return 0;
+    }
     int flush() {
         const int cnt = pl.elem == 8 ? b64.count : b32.count;
         if (cnt == 0) return 0;
         size_t ev;
         CHECK(prof_begin(h, PROF_GEMM, cnt, cnt * sym_product_flop(pl.n), 0.0, &ev));
         hipError_t e = hipSuccess;
-        if (pl.elem == 8) e = launch_gemm_f64(b64, pl.n, pl.ld, h->stream, h->gemm_scratch,
+        if (pl.elem == 8 && h->rns_slots > 0) CHECK(flush_rns());
+        else if (pl.elem == 8) e = launch_gemm_f64(b64, pl.n, pl.ld, h->stream, h->gemm_scratch,
                                               h->gemm_scratch ? kGemmScratchBytes : 0);
         else e = launch_gemm_f32(b32, pl.n, pl.ld,
                                  pl.prec == CHEBDM_BF16X6 ? 2 : (pl.prec == CHEBDM_BF16X3 ? 1 : 0), h->stream,
@@ -437,7 +557,7 @@ int odd_chain_step(int K) {
 struct ReplayKey {
     int32_t kind, order, k, m, prec, form, baby, ladder, search, max_iter, bounds_on_device, damping, split_h, split_q;
     int64_t n, ld, ldh, ldd, M;
-    const void *dH, *dD, *mats, *small;
+    const void *dH, *dD, *mats, *small, *rns;   // rns: null when the products run on the float64 units
     double tol, beta, x, emin, emax;   // x: n_elec (mu search) or mu (density)
 };
 
@@ -469,6 +589,7 @@ std::vector<char> replay_key(int kind, const Plan& pl, chebdm_handle h, const do
     k.dD = dD;
     k.mats = h->mats;
     k.small = h->small;
+    k.rns = h->rns_slots > 0 ? h->rns : nullptr;
     k.tol = pl.tol;
     k.beta = beta;
     k.x = x;
@@ -689,6 +810,7 @@ int giant_steps(chebdm_handle h, const Plan& pl, double* dD, int64_t ldd, int* n
         HIP_TRY(launch_combine<float>((const float*)tslot(h, pl, 1), stride, k, m, h->coef,
                                       (float*)rslot(h, pl, 0), pl.n, pl.ld, h->stream));
     CHECK(prof_end(h, ev));
+    rns_forget(h, rslot(h, pl, 0), rslot(h, pl, m));   // the ladder's matrices made room for the blocks
     if (m == 1) {
         HIP_TRY(launch_copy_out(rslot(h, pl, 0), pl.elem == 8, pl.ld, pl.n, dD, ldd, h->stream));
     } else {
@@ -841,6 +963,7 @@ int chebdm_destroy(chebdm_handle h) {
     if (h->small) (void)hipFree(h->small);
     if (h->lz) (void)hipFree(h->lz);
     if (h->gemm_scratch) (void)hipFree(h->gemm_scratch);
+    if (h->rns) (void)hipFree(h->rns);
     if (h->mlp_work) (void)hipFree(h->mlp_work);
     if (h->h_scal) (void)hipHostFree(h->h_scal);
     delete h;
@@ -991,9 +1114,11 @@ int chebdm_density(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, do
     CHECK(ensure_small(h, pl.M));
     pl.ld = round_up(n, 128);
     CHECK(ensure_mats(h, pl, pl.k + pl.m));
+    CHECK(ensure_rns(h, pl));
     const std::vector<char> key = replay_key(2, pl, h, dH, ldh, dD, ldd, beta, mu, bounds_dev, emin, emax);
     CHECK(run_replayed(h, 2, key, &pl.n_gemm, [&]() -> int {
         pl.n_gemm = 0;
+        rns_reset(h);
         HIP_TRY(launch_set_scalars(h->scal, emin, emax, beta, mu, 1, 0.0, pl.tol, pl.max_iter, h->stream,
                                    bounds_dev));
         HIP_TRY(launch_shift(dH, n, ldh, h->scal, tslot(h, pl, 1), pl.ld, pl.prec, h->stream));
@@ -1044,11 +1169,13 @@ int chebdm_mu_search(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, 
     pl.split_h = two_chain_split(pl, dD != nullptr);
     pl.split_q = four_chain_split(pl, pl.split_h);
     CHECK(ensure_mats(h, pl, pl.k + pl.m + extra_chain_slots(pl)));
+    CHECK(ensure_rns(h, pl));
     const int slot = dD ? 0 : 1;
     const std::vector<char> key = replay_key(slot, pl, h, dH, ldh, dD, dD ? ldd : 0, beta, n_elec, bounds_dev,
                                              emin, emax);
     CHECK(run_replayed(h, slot, key, &pl.n_gemm, [&]() -> int {
         pl.n_gemm = 0;
+        rns_reset(h);
         HIP_TRY(launch_set_scalars(h->scal, emin, emax, beta, 0.0, 0, n_elec, pl.tol, pl.max_iter, h->stream,
                                    bounds_dev));
         HIP_TRY(launch_shift(dH, n, ldh, h->scal, tslot(h, pl, 1), pl.ld, pl.prec, h->stream));
@@ -1120,6 +1247,8 @@ int chebdm_moments(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, in
     CHECK(ensure_small(h, 0));
     pl.ld = round_up(n, 128);
     CHECK(ensure_mats(h, pl, pl.k + pl.m));
+    CHECK(ensure_rns(h, pl));
+    rns_reset(h);
     HIP_TRY(launch_set_scalars(h->scal, emin, emax, 1.0, 0.0, 0, 0.0, pl.tol, pl.max_iter, h->stream));
     HIP_TRY(launch_shift(dH, n, ldh, h->scal, tslot(h, pl, 1), pl.ld, pl.prec, h->stream));
     CHECK(baby_steps(h, pl, &pl.n_gemm));

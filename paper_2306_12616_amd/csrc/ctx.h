@@ -50,6 +50,16 @@ struct chebdm_ctx {
     Replay replay[4];            // mu search with D, mu search without D, density, Lanczos bounds
     // partial accumulators of K-sliced tail tiles of the products, kGemmScratchBytes
     void* gemm_scratch = nullptr;
+    // residue planes of float64 products (k_rns.hip): operand sets (least recently used one
+    // replaced), their row scales, and the residues of one launch's products
+    void* rns = nullptr;
+    size_t rns_bytes = 0;
+    chebdm::RnsGeom rns_geo{};
+    int rns_slots = 0;                        // 0: products run on the float64 units
+    int64_t rns_res_products = 0;
+    std::vector<const void*> rns_owner;       // matrix whose planes a slot holds
+    std::vector<int64_t> rns_used;
+    int64_t rns_clock = 0;
     // Lanczos bounds workspace (basis, work vectors, partials, tridiagonal)
     double* lz = nullptr;
     int64_t lz_doubles = 0;

@@ -127,6 +127,35 @@ hipError_t launch_gemm_f64(const GemmBatch<double>& b, int64_t n, int64_t ld, hi
 hipError_t launch_gemm_f32(const GemmBatch<float>& b, int64_t n, int64_t ld, int split, hipStream_t st,
                            void* scratch = nullptr, size_t scratch_bytes = 0);
 
+// ---- float64 products by residue arithmetic on int8 MFMA (k_rns.hip)
+constexpr int kRnsModuli = 15;
+constexpr int kRnsGroup = 16;   // operands or products of one launch
+struct RnsGeom {                // sizes that follow from n
+    int64_t n, rows;            // rows: n rounded up to the tile
+    int kt;                     // K steps of 64
+    int64_t plane_bytes;        // one modulus of one operand
+    int64_t set_bytes;          // all moduli of one operand
+    int ntr, ntc, ntiles;       // tile rows, tile columns, tiles on and above the diagonal
+    int64_t res_bytes;          // residues of one product
+    bool big;                   // 256 x 128 tiles (else 128 x 128)
+};
+RnsGeom rns_geom(int64_t n);
+struct RnsProduct {             // Out = alpha A B + beta C + gamma E + delta I (C, E may be null)
+    const int8_t *planes_a, *planes_b;
+    const double *scale_a, *scale_b;   // of launch_rns_split (2 rows doubles)
+    const double *C, *E;               // ld x ld workspace matrices
+    double* Out;
+    int64_t ld_out;
+    double alpha, beta, gamma, delta;
+    int64_t vec;                       // set by the launch
+};
+// Row scales and residue planes of `count` symmetric ld x ld matrices (ld even, zero padding).
+hipError_t launch_rns_split(const RnsGeom& g, int64_t ld, const double* const* mats, int8_t* const* planes,
+                            double* const* scale, int count, hipStream_t st);
+// res: count * g.res_bytes
+hipError_t launch_rns_products(const RnsGeom& g, int64_t ld, const RnsProduct* prods, int count, int8_t* res,
+                               hipStream_t st);
+
 }  // namespace chebdm
 
 // ======================================================================
