@@ -73,7 +73,7 @@ struct chebdm_batch_ctx {
     int search_mode = 0;
     const float* mlp_w = nullptr;
     double mlp_delta = 0.02;
-    float *feat = nullptr, *mu_hat = nullptr, *mlp_work = nullptr;
+    float *feat = nullptr, *mu_hat = nullptr;
     // Lanczos bounds (opts.bounds): per-problem workspace, steps and margin; lz == nullptr: Gershgorin
     double* lz = nullptr;
     int64_t lz_stride = 0;
@@ -228,7 +228,7 @@ int enqueue(chebdm_batch_ctx* b, hipStream_t st, bool prof, bool with_density) {
     if (prof) CHECK(prof_begin(b->h, PROF_SEARCH, 0, 0.0, 0.0, &ev));
     if (b->search_mode == 2) {
         HIP_TRY(launch_batch_features(d, b->geo, b->tau, b->scal, b->feat, st));
-        HIP_TRY(launch_mlp_forward(b->mlp_w, b->feat, d.count, b->mu_hat, b->mlp_work, st));
+        HIP_TRY(launch_mlp_forward(b->mlp_w, b->feat, d.count, b->mu_hat, st));
     }
     HIP_TRY(launch_batch_search(d, b->tau, b->mq, b->w, b->x, b->scal, b->search_mode, b->mu_hat, b->mlp_delta,
                                 b->ftab, st));
@@ -418,7 +418,6 @@ int chebdm_batch_create(chebdm_handle h, int32_t count, const int64_t* n, int32_
     const size_t o_c = take(sizeof(double) * C * L1), o_coef = take(sizeof(double) * C * K * M);
     const size_t o_mu = take(sizeof(double) * C), o_trd = take(sizeof(double) * C);
     const size_t o_feat = take(sizeof(float) * C * 64), o_muh = take(sizeof(float) * C);
-    const size_t o_mlpw = take(sizeof(float) * C * 512);
     if (hipMalloc(&b->dev, bytes) != hipSuccess) {
         b->dev = nullptr;
         (void)hipGetLastError();
@@ -445,7 +444,6 @@ int chebdm_batch_create(chebdm_handle h, int32_t count, const int64_t* n, int32_
     b->trD = (double*)(base + o_trd);
     b->feat = (float*)(base + o_feat);
     b->mu_hat = (float*)(base + o_muh);
-    b->mlp_work = (float*)(base + o_mlpw);
     const size_t hbytes = sizeof(BatchProblem) * C + sizeof(DevScalars) * C + 2 * sizeof(double) * C + 256;
     if (hipHostMalloc(&b->host, hbytes, hipHostMallocDefault) != hipSuccess) {
         b->host = nullptr;

@@ -35,8 +35,7 @@ int chebdm_mlp_forward(chebdm_handle h, const float* dW, const float* dX, int32_
     if (!h || !dW || !dX || !dY) return fail(CHEBDM_ERR_ARG, "NULL argument");
     if (batch < 1) return fail(CHEBDM_ERR_ARG, "batch must be >= 1");
     HIP_TRY(hipSetDevice(h->device));
-    CHECK(ensure_mlp_work(h, 2 * (int64_t)batch * 256));
-    HIP_TRY(launch_mlp_forward(dW, dX, batch, dY, h->mlp_work, h->stream));
+    HIP_TRY(launch_mlp_forward(dW, dX, batch, dY, h->stream));
     return CHEBDM_OK;
 }
 
@@ -45,7 +44,7 @@ int chebdm_mlp_backward(chebdm_handle h, const float* dW, const float* dX, const
     if (!h || !dW || !dX || !dT || !dGrad) return fail(CHEBDM_ERR_ARG, "NULL argument");
     if (batch < 1) return fail(CHEBDM_ERR_ARG, "batch must be >= 1");
     HIP_TRY(hipSetDevice(h->device));
-    const int64_t floats = 4 * (int64_t)batch * 256 + 2 * (int64_t)batch + 1;
+    const int64_t floats = 4 * (int64_t)batch * 256 + 2 * (int64_t)batch + 2 * (((int64_t)batch + 15) / 16) + 1;
     CHECK(ensure_mlp_work(h, floats));
     float* loss = h->mlp_work + floats - 1;
     HIP_TRY(launch_mlp_backward(dW, dX, dT, batch, dGrad, h->mlp_work, loss, h->stream));

@@ -234,8 +234,8 @@ hipError_t launch_batch_finish(const BatchDims& d, const BatchProblem* tab, cons
 // ---- learned chemical potential (k_mlp.hip): 64 -> 256 -> 256 -> 1, ReLU, float32
 namespace chebdm {
 int64_t mlp_nparams();
-// work: 4 * B * 256 + 2 * B + 1 floats for backward (2 * B * 256 for forward)
-hipError_t launch_mlp_forward(const float* w, const float* X, int Bn, float* y, float* work, hipStream_t st);
+// work: 4 * B * 256 + 2 * B + 2 * ceil(B / 16) floats, 8-byte aligned
+hipError_t launch_mlp_forward(const float* w, const float* X, int Bn, float* y, hipStream_t st);
 hipError_t launch_mlp_backward(const float* w, const float* X, const float* t, int Bn, float* g, float* work,
                                float* loss, hipStream_t st);
 hipError_t launch_mlp_adam(float* w, const float* g, float* m, float* v, int64_t n, float lr, float b1, float b2,

@@ -84,6 +84,29 @@ def test_forward_backward_match_oracle(cd, handle, batch):
         assert err <= 1e-4 * ref + 1e-12, (name, err, ref)
 
 
+@pytest.mark.parametrize("batch", [15, 16, 17, 65, 129])
+def test_row_blocks_and_unaligned_weights(cd, handle, batch):
+    # edges of the 16-row blocks and of the gradients' 64-row steps, with the weights at a 4-byte offset
+    # (float32 sums of at most 256 terms: 256 * 2^-24 of the largest term, 1e-4 as above)
+    print(f"row blocks batch={batch}", flush=True)
+    rng = np.random.default_rng(batch)
+    w32 = _params32(9)
+    X32 = rng.normal(0, 1, (batch, 64)).astype(np.float32)
+    T32 = rng.normal(0, 0.2, batch).astype(np.float32)
+    W = torch.zeros(w32.size + 1, device="cuda")[1:]
+    W.copy_(torch.from_numpy(w32))
+    X, T = torch.from_numpy(X32).cuda(), torch.from_numpy(T32).cuda()
+    y = cd.chebdm_mlp_forward(handle, W, X).cpu().numpy()
+    y_ref, _ = om.forward(w32.astype(np.float64), X32.astype(np.float64))
+    assert np.max(np.abs(y - y_ref)) <= 1e-5 * max(1.0, float(np.max(np.abs(y_ref))))
+    g, loss = cd.chebdm_mlp_backward(handle, W, X, T)
+    L_ref, g_ref = om.backward(w32.astype(np.float64), X32.astype(np.float64), T32.astype(np.float64))
+    assert abs(loss - L_ref) <= 1e-5 * L_ref
+    gd, gr = _blocks(g.cpu().numpy().astype(np.float64)), _blocks(g_ref)
+    for name in gr:
+        assert np.max(np.abs(gd[name] - gr[name])) <= 1e-4 * np.max(np.abs(gr[name])) + 1e-12, name
+
+
 def test_adam_matches_oracle(cd, handle):
     rng = np.random.default_rng(3)
     n = cd.chebdm_mlp_num_params()
