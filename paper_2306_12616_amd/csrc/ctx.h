@@ -26,6 +26,7 @@ struct chebdm_ctx {
     // pinned host mirror for read-backs
     chebdm::DevScalars* h_scal = nullptr;
     double* h_trD = nullptr;
+    double* h_extra = nullptr;   // 2 kMaxLanczosSteps + 1 doubles
     // optional launch timing: HIP events recorded on the handle's stream
     struct Ev {
         hipEvent_t a = nullptr, b = nullptr;

@@ -70,6 +70,10 @@ hipError_t launch_fill_identity(double* D, int64_t n, int64_t ldd, double value,
 hipError_t launch_copy_out(const void* src, int is_f64, int64_t ld, int64_t n, double* D, int64_t ldd,
                            hipStream_t st);
 
+// device scalars, *trD and count doubles of extra into pinned host memory
+hipError_t launch_publish(const DevScalars* s, const double* trD, const double* extra, int count, DevScalars* h_s,
+                          double* h_trD, double* h_extra, hipStream_t st);
+
 // ---- commutator check (k_check.hip): *out = max |H D - D H| (float64 bits written as a double);
 // Hw, Dw: ld x ld workspace matrices with zero padding (ld a multiple of 64)
 hipError_t launch_commutator(const double* H, int64_t ldh, const double* D, int64_t ldd, int64_t n, int64_t ld,
@@ -78,8 +82,9 @@ hipError_t launch_commutator(const double* H, int64_t ldh, const double* D, int6
 // ---- Lanczos bounds (k_lanczos.hip)
 constexpr int kMaxLanczosSteps = 128;
 struct LanczosWork {          // views into one device buffer of lanczos_work_doubles(n, steps) doubles
-    double *V, *w, *w2;        // basis v_0..v_{steps-1} (rows of n), work vectors
-    double *pa, *pc, *pn;      // per-block partials: alpha, projections, norm
+    double *V, *Z, *w;         // basis v_0..v_{steps-1} and H v_i (rows of n), work vector
+    double *pa, *pv, *pz, *pn; // per-block partials: alpha, v_i . w, z_i . w, norm
+    double* g;                 // v_i . v_j of the last two steps
     double *alpha, *beta;      // tridiagonal T (steps each)
     int32_t* state;            // [0]: steps done at a breakdown (0: none), [1]: steps done
 };
