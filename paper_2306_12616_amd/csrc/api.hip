@@ -520,6 +520,7 @@ struct Chain {
         CHECK(prof_begin(h, PROF_GEMM, cnt, cnt * sym_product_flop(pl.n), 0.0, &ev));
         hipError_t e = hipSuccess;
         if (pl.elem == 8 && h->rns_slots > 0) CHECK(flush_rns());
+        else if (pl.elem == 8 && gemm_small_pays(pl.n, cnt)) e = launch_gemm_small(b64, pl.n, pl.ld, h->stream);
         else if (pl.elem == 8) e = launch_gemm_f64(b64, pl.n, pl.ld, h->stream, h->gemm_scratch,
                                               h->gemm_scratch ? kGemmScratchBytes : 0);
         else e = launch_gemm_f32(b32, pl.n, pl.ld,

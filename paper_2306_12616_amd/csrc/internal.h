@@ -132,6 +132,10 @@ hipError_t launch_gemm_f64(const GemmBatch<double>& b, int64_t n, int64_t ld, hi
 hipError_t launch_gemm_f32(const GemmBatch<float>& b, int64_t n, int64_t ld, int split, hipStream_t st,
                            void* scratch = nullptr, size_t scratch_bytes = 0);
 
+// ---- float64 products of small matrices (k_small.hip)
+bool gemm_small_pays(int64_t n, int count);
+hipError_t launch_gemm_small(const GemmBatch<double>& b, int64_t n, int64_t ld, hipStream_t st);
+
 // ---- float64 products by residue arithmetic on int8 MFMA (k_rns.hip)
 constexpr int kRnsModuli = 15;
 constexpr int kRnsGroup = 16;   // operands or products of one launch
