@@ -257,16 +257,12 @@ void* slot(chebdm_handle h, const Plan& pl, int64_t s) {
     return static_cast<char*>(h->mats) + (size_t)s * (size_t)pl.ld * (size_t)pl.ld * pl.elem;
 }
 
-// Scalars and tr D (and `count` doubles more) into the handle's pinned mirror: one small launch that
-// writes host memory, in place of a copy command each (about 3 us and a gap of 6-20 us apiece).
-int publish_scalars(chebdm_handle h, const double* extra = nullptr, int count = 0) {
-    HIP_TRY(launch_publish(h->scal, h->trD, extra, count, h->h_scal, h->h_trD, h->h_extra, h->stream));
-    return 0;
-}
-
-int read_scalars(chebdm_handle h, const double* extra = nullptr, int count = 0) {
-    CHECK(publish_scalars(h, extra, count));
-    HIP_TRY(hipStreamSynchronize(h->stream));
+// Scalars, tr D (where D is given) and `count` doubles more into the handle's pinned mirror: one
+// small launch that writes host memory, in place of a copy command each (about 3 us and a gap of
+// 6-20 us apiece).
+int publish_scalars(chebdm_handle h, const double* D, int64_t n, int64_t ldd, const double* extra = nullptr,
+                    int count = 0) {
+    HIP_TRY(launch_publish(h->scal, h->trD, D, n, ldd, extra, count, h->h_scal, h->h_trD, h->h_extra, h->stream));
     return 0;
 }
 
@@ -377,10 +373,12 @@ int resolve_bounds(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, do
                    const Plan* pl = nullptr) {
     if (std::isnan(emin) || std::isnan(emax)) {
         CHECK(ensure_small(h, 0));
-        HIP_TRY(launch_gershgorin(dH, n, ldh, h->partial, kPartialDoubles, h->scal, h->stream));
-        if (pl && pl->bounds == CHEBDM_BOUNDS_LANCZOS)
+        HIP_TRY(launch_gershgorin(dH, n, ldh, h->partial, kPartialDoubles, h->scal, h->stream, h->h_scal));
+        if (pl && pl->bounds == CHEBDM_BOUNDS_LANCZOS) {
             CHECK(lanczos_on_device(h, dH, n, ldh, pl->lz_steps, pl->lz_margin, 0));
-        CHECK(read_scalars(h));
+            CHECK(publish_scalars(h, nullptr, 0, 0));
+        }
+        HIP_TRY(hipStreamSynchronize(h->stream));
         if (h->h_scal->nonfinite) return fail(CHEBDM_ERR_NONFINITE, "H holds NaN or Inf");
         emin = h->h_scal->emin;
         emax = h->h_scal->emax;
@@ -804,7 +802,7 @@ int moments_on_device(chebdm_handle h, const Plan& pl, int* n_gemm) {
     return 0;
 }
 
-// Block sums R_l (or S_j) and the giant steps; writes D (ldd) and its trace.
+// Block sums R_l (or S_j) and the giant steps; writes D (ldd).
 int giant_steps(chebdm_handle h, const Plan& pl, double* dD, int64_t ldd, int* n_gemm) {
     const int k = pl.k, m = pl.m;
     const int64_t stride = pl.ld * pl.ld;
@@ -853,7 +851,7 @@ int giant_steps(chebdm_handle h, const Plan& pl, double* dD, int64_t ldd, int* n
         } else if (pl.form == CHEBDM_GIANT_COMPOSITION && pl.split_h > 0) {
             // two Clenshaw chains in Y = T_k, advanced together (two products per launch):
             // S_A = sum_{l<h} T_l(Y) R''_l over R slots 0..h-1 and S_B = sum_{j<m-h} T_j(Y) R'_j
-            // over R slots h..m-1 (blocks rearranged by launch_split_blocks), then
+            // over R slots h..m-1 (blocks rearranged by launch_block_coeffs), then
             // D = S_A + T_h(Y) S_B with T_h(Y) = T_{hk} kept from the ladder.
             const int hs = pl.split_h;
             const int la = hs, lb = m - hs;   // chain lengths (terms)
@@ -892,7 +890,6 @@ int giant_steps(chebdm_handle h, const Plan& pl, double* dD, int64_t ldd, int* n
             CHECK(ch.flush());
         }
     }
-    HIP_TRY(launch_trace_f64(dD, pl.n, ldd, h->trD, h->stream));
     return 0;
 }
 
@@ -1009,7 +1006,8 @@ int chebdm_bounds_lanczos(chebdm_handle h, const double* dH, int64_t n, int64_t 
     CHECK(lanczos_on_device(h, dH, n, ldh, steps, margin, seed));
     const int k = (int)std::min<int64_t>(steps, n);
     const LanczosWork L = lanczos_layout(h->lz, n, k);
-    CHECK(read_scalars(h, L.alpha, 2 * k + 1));   // alpha, beta and the state lie one after the other
+    CHECK(publish_scalars(h, nullptr, 0, 0, L.alpha, 2 * k + 1));   // alpha, beta, state: one after the other
+    HIP_TRY(hipStreamSynchronize(h->stream));
     const double* ab = h->h_extra;
     int32_t st[2];
     std::memcpy(st, ab + 2 * k, sizeof(st));
@@ -1137,7 +1135,8 @@ int chebdm_density(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, do
         return 0;
     }));
     if (info) {
-        CHECK(read_scalars(h));
+        CHECK(publish_scalars(h, dD, n, ldd));
+        HIP_TRY(hipStreamSynchronize(h->stream));
         fill_info(info, pl, emin, emax, mu, *h->h_trD, 0.0, 0, CHEBDM_OK);
     }
     return CHEBDM_OK;
@@ -1192,20 +1191,14 @@ int chebdm_mu_search(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, 
         size_t ev = (size_t)-1;
         if (h->prof) CHECK(prof_begin(h, PROF_SEARCH, 0, 0.0, 0.0, &ev));
         HIP_TRY(launch_dct3(h->tau, order, pl.M, h->w, h->xtab, h->stream, pl.damping));
-        HIP_TRY(launch_bisect(h->w, h->xtab, pl.M, h->scal, pl.search, h->ftab, h->stream));
+        HIP_TRY(launch_bisect(h->w, h->xtab, pl.M, h->scal, pl.search, h->ftab, h->partial, h->stream));
         if (h->prof) CHECK(prof_end(h, ev));
         if (dD) {
             HIP_TRY(launch_fermi_coeffs(order, pl.M, h->scal, h->ftab, h->c, h->stream, pl.damping));
-            HIP_TRY(launch_block_coeffs(h->c, order, pl.k, pl.m, pl.form, h->coef, h->stream));
-            if (pl.split_h > 0) HIP_TRY(launch_split_blocks(h->coef, pl.k, pl.m, pl.split_h, h->stream));
-            if (pl.split_q > 0) {
-                HIP_TRY(launch_split_blocks(h->coef, pl.k, pl.split_h, pl.split_q, h->stream));
-                HIP_TRY(launch_split_blocks(h->coef + (int64_t)pl.split_h * pl.k, pl.k, pl.m - pl.split_h,
-                                            pl.split_q, h->stream));
-            }
+            HIP_TRY(launch_block_coeffs(h->c, order, pl.k, pl.m, pl.form, h->coef, h->stream, pl.split_h, pl.split_q));
             CHECK(giant_steps(h, pl, dD, ldd, &pl.n_gemm));
         }
-        return publish_scalars(h);
+        return publish_scalars(h, dD, n, ldd);
     }));
     HIP_TRY(hipStreamSynchronize(h->stream));
     const DevScalars& s = *h->h_scal;

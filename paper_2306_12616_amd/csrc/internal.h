@@ -56,7 +56,7 @@ struct GemmBatch {
 
 // ---- bounds / shift / traces (k_bounds.hip)
 hipError_t launch_gershgorin(const double* H, int64_t n, int64_t ldh, double* partial,
-                             int64_t partial_cap, DevScalars* s, hipStream_t st);
+                             int64_t partial_cap, DevScalars* s, hipStream_t st, DevScalars* h_s = nullptr);
 hipError_t launch_set_scalars(DevScalars* s, double emin, double emax, double beta, double mu,
                               int has_mu, double n_elec, double tol, int max_iter, hipStream_t st,
                               int bounds_on_device = 0);
@@ -65,14 +65,15 @@ hipError_t launch_shift(const double* H, int64_t n, int64_t ldh, const DevScalar
 // traces of `count` matrices spaced `stride` elements apart (float or double), into out[0..count)
 hipError_t launch_traces(const void* base, int64_t stride, int count, int64_t n, int64_t ld,
                          int is_f64, double* out, hipStream_t st);
-hipError_t launch_trace_f64(const double* D, int64_t n, int64_t ld, double* out, hipStream_t st);
 hipError_t launch_fill_identity(double* D, int64_t n, int64_t ldd, double value, hipStream_t st);
 hipError_t launch_copy_out(const void* src, int is_f64, int64_t ld, int64_t n, double* D, int64_t ldd,
                            hipStream_t st);
 
-// device scalars, *trD and count doubles of extra into pinned host memory
-hipError_t launch_publish(const DevScalars* s, const double* trD, const double* extra, int count, DevScalars* h_s,
-                          double* h_trD, double* h_extra, hipStream_t st);
+// device scalars and count doubles of extra into pinned host memory; with D (n x n) also tr D, into
+// *trD and *h_trD
+hipError_t launch_publish(const DevScalars* s, double* trD, const double* D, int64_t n, int64_t ldd,
+                          const double* extra, int count, DevScalars* h_s, double* h_trD, double* h_extra,
+                          hipStream_t st);
 
 // ---- commutator check (k_check.hip): *out = max |H D - D H| (float64 bits written as a double);
 // Hw, Dw: ld x ld workspace matrices with zero padding (ld a multiple of 64)
@@ -99,17 +100,19 @@ hipError_t launch_lanczos(const double* H, int64_t n, int64_t ldh, int steps, do
 // ---- coefficients / decomposition / moments / bisection (k_cheb.hip)
 hipError_t launch_fermi_coeffs(int order, int M, const DevScalars* s, double* f_tab, double* c_out,
                                hipStream_t st, int damping = 0);
+// split_h > 0: composition-form blocks rearranged for two Clenshaw chains split at h (m - h <= h);
+// split_q > 0: each of them again at q
 hipError_t launch_block_coeffs(const double* c, int order, int k, int m, int form, double* coef,
-                               hipStream_t st);
-// composition-form blocks rearranged for two Clenshaw chains split at h (m - h <= h)
-hipError_t launch_split_blocks(double* coef, int k, int m, int h, hipStream_t st);
+                               hipStream_t st, int split_h = 0, int split_q = 0);
 hipError_t launch_assemble_moments(const double* tr_baby, const double* gram, int k, int m,
                                    int order, int64_t n, double* tau, hipStream_t st);
 hipError_t launch_dct3(const double* tau, int order, int M, double* w, double* x_tab, hipStream_t st,
                        int damping = 0);
-// scratch: M doubles of device memory, free during the call (the Fermi table's buffer)
+// scratch: M doubles of device memory, free during the call (the Fermi table's buffer); work:
+// kSearchWork more
+constexpr int kSearchWork = 4096;
 hipError_t launch_bisect(const double* w, const double* x_tab, int M, DevScalars* s, int mode, double* scratch,
-                         hipStream_t st);
+                         double* work, hipStream_t st);
 
 // ---- block sums and Gram contractions (k_combine.hip)
 // R_l = sum_{i<k} coef[l*k + i] T_i for l < m (T_0 = I implicit, T_i = tbase + (i-1)*stride)

@@ -37,31 +37,35 @@ k_gersh_partial(const double* __restrict__ H, int64_t n, int64_t ldh, int64_t ro
 
 constexpr int kColThreads = 256;
 
-// Per column j: r_j = sum of the split partials (fixed order), the disc [d - r_j, d + r_j]
-// with d = H[j][j]; per work-group: min, max and a non-finite flag, written to out[3][nb].
+// Column j: r_j = sum of the split partials in order (sixteen loads in flight; one load per addition
+// took 20 us at N = 2000), the disc [d - r_j, d + r_j] with d = H[j][j].
+__device__ __forceinline__ void column_disc(const double* __restrict__ H, int64_t n, int64_t ldh,
+                                            const double* __restrict__ partial, int nsplit, int64_t j, double& lo,
+                                            double& hi, double& bad) {
+    double r = 0.0;
+    const double d = H[j * ldh + j];
+    int sp = 0;
+    for (; sp + 16 <= nsplit; sp += 16) {
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = partial[(int64_t)(sp + u) * n + j];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) r += v[u];
+    }
+    for (; sp < nsplit; ++sp) r += partial[(int64_t)sp * n + j];
+    if (!isfinite(r) || !isfinite(d)) bad = 1.0;
+    lo = d - r;
+    hi = d + r;
+}
+
+// Per work-group of columns: min, max and a non-finite flag, written to out[3][nb].
 __global__ void __launch_bounds__(kColThreads)
 k_gersh_cols(const double* __restrict__ H, int64_t n, int64_t ldh, const double* __restrict__ partial, int nsplit,
              double* __restrict__ out, int nb) {
     __shared__ double smem[kColThreads / 64];
     const int64_t j = (int64_t)blockIdx.x * kColThreads + threadIdx.x;
     double lo = INFINITY, hi = -INFINITY, bad = 0.0;
-    if (j < n) {
-        double r = 0.0;
-        // sixteen loads in flight, added in order (a load per addition: 20 us at N = 2000)
-        int sp = 0;
-        for (; sp + 16 <= nsplit; sp += 16) {
-            double v[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = partial[(int64_t)(sp + u) * n + j];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) r += v[u];
-        }
-        for (; sp < nsplit; ++sp) r += partial[(int64_t)sp * n + j];
-        const double d = H[j * ldh + j];
-        if (!isfinite(r) || !isfinite(d)) bad = 1.0;
-        lo = d - r;
-        hi = d + r;
-    }
+    if (j < n) column_disc(H, n, ldh, partial, nsplit, j, lo, hi, bad);
     bad = block_sum<kColThreads>(bad, smem);
     lo = block_min<kColThreads>(lo, smem);
     hi = block_max<kColThreads>(hi, smem);
@@ -72,10 +76,36 @@ k_gersh_cols(const double* __restrict__ H, int64_t n, int64_t ldh, const double*
     }
 }
 
+// The bounds into the scalars, and into their host mirror where one is given.
+__device__ __forceinline__ void put_bounds(DevScalars* s, double lo, double hi, int bad) {
+    if (!s) return;
+    s->emin = lo;
+    s->emax = hi;
+    s->nonfinite = bad;
+}
+
+// Up to kOneFold columns: columns and result in one launch.
+constexpr int kOneFold = 1024;
+
+__global__ void __launch_bounds__(kOneFold)
+k_gersh_fold(const double* __restrict__ H, int64_t n, int64_t ldh, const double* __restrict__ partial, int nsplit,
+             DevScalars* s, DevScalars* h_s) {
+    __shared__ double smem[kOneFold / 64];
+    double lo = INFINITY, hi = -INFINITY, bad = 0.0;
+    if ((int)threadIdx.x < n) column_disc(H, n, ldh, partial, nsplit, threadIdx.x, lo, hi, bad);
+    bad = block_sum<kOneFold>(bad, smem);
+    lo = block_min<kOneFold>(lo, smem);
+    hi = block_max<kOneFold>(hi, smem);
+    if (threadIdx.x == 0) {
+        put_bounds(s, lo, hi, bad > 0.0 ? 1 : 0);
+        put_bounds(h_s, lo, hi, bad > 0.0 ? 1 : 0);
+    }
+}
+
 constexpr int kFinalThreads = 256;
 
 __global__ void __launch_bounds__(kFinalThreads)
-k_gersh_final(const double* __restrict__ part, int nb, DevScalars* s) {
+k_gersh_final(const double* __restrict__ part, int nb, DevScalars* s, DevScalars* h_s) {
     __shared__ double smem[kFinalThreads / 64];
     double lo = INFINITY, hi = -INFINITY, bad = 0.0;
     for (int b = threadIdx.x; b < nb; b += kFinalThreads) {
@@ -87,9 +117,8 @@ k_gersh_final(const double* __restrict__ part, int nb, DevScalars* s) {
     lo = block_min<kFinalThreads>(lo, smem);
     hi = block_max<kFinalThreads>(hi, smem);
     if (threadIdx.x == 0) {
-        s->emin = lo;
-        s->emax = hi;
-        s->nonfinite = bad > 0.0 ? 1 : 0;
+        put_bounds(s, lo, hi, bad > 0.0 ? 1 : 0);
+        put_bounds(h_s, lo, hi, bad > 0.0 ? 1 : 0);
     }
 }
 
@@ -136,22 +165,30 @@ k_copy_out(const T* __restrict__ src, int64_t ld, int64_t n, double* __restrict_
     D[i * ldd + j] = (double)src[i * ld + j];
 }
 
+// D != nullptr: tr D first, into *trD.
 __global__ void __launch_bounds__(256)
-k_publish(const double* __restrict__ s, const double* __restrict__ trD, const double* __restrict__ extra, int count,
-          double* h_s, double* h_trD, double* h_extra) {
+k_publish(const double* __restrict__ s, double* __restrict__ trD, const double* __restrict__ D, int64_t n, int64_t ldd,
+          const double* __restrict__ extra, int count, double* h_s, double* h_trD, double* h_extra) {
+    __shared__ double smem[4];
     const int t = threadIdx.x;
     if (t < (int)(sizeof(DevScalars) / sizeof(double))) h_s[t] = s[t];
-    if (t == 255) *h_trD = *trD;
     for (int i = t; i < count; i += 256) h_extra[i] = extra[i];
+    if (D) {
+        double acc = 0.0;
+        for (int64_t i = t; i < n; i += 256) acc += D[i * ldd + i];
+        acc = block_sum<256>(acc, smem);
+        if (t == 0) *trD = *h_trD = acc;
+    }
 }
 
 }  // namespace
 
-hipError_t launch_publish(const DevScalars* s, const double* trD, const double* extra, int count, DevScalars* h_s,
-                          double* h_trD, double* h_extra, hipStream_t st) {
+hipError_t launch_publish(const DevScalars* s, double* trD, const double* D, int64_t n, int64_t ldd,
+                          const double* extra, int count, DevScalars* h_s, double* h_trD, double* h_extra,
+                          hipStream_t st) {
     static_assert(sizeof(DevScalars) % sizeof(double) == 0, "copied as doubles");
-    hipLaunchKernelGGL(k_publish, dim3(1), dim3(256), 0, st, reinterpret_cast<const double*>(s), trD, extra, count,
-                       reinterpret_cast<double*>(h_s), h_trD, h_extra);
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(256), 0, st, reinterpret_cast<const double*>(s), trD, D, n, ldd, extra,
+                       count, reinterpret_cast<double*>(h_s), h_trD, h_extra);
     return hipGetLastError();
 }
 
@@ -172,7 +209,7 @@ hipError_t launch_copy_out(const void* src, int is_f64, int64_t ld, int64_t n, d
 }
 
 hipError_t launch_gershgorin(const double* H, int64_t n, int64_t ldh, double* partial,
-                             int64_t partial_cap, DevScalars* s, hipStream_t st) {
+                             int64_t partial_cap, DevScalars* s, hipStream_t st, DevScalars* h_s) {
     const int64_t col_blocks = (n + kColsPerBlock - 1) / kColsPerBlock;
     int64_t nsplit = (2048 + col_blocks - 1) / col_blocks;
     const int64_t max_split = (n + 31) / 32;
@@ -186,9 +223,15 @@ hipError_t launch_gershgorin(const double* H, int64_t n, int64_t ldh, double* pa
     double* part2 = partial + nsplit * n;
     hipLaunchKernelGGL(k_gersh_partial, dim3((unsigned)col_blocks, (unsigned)nsplit), dim3(kColsPerBlock),
                        0, st, H, n, ldh, rows_per_split, partial);
+    if (n <= kOneFold) {
+        hipLaunchKernelGGL(k_gersh_fold, dim3(1), dim3(kOneFold), 0, st, H, n, ldh, (const double*)partial, (int)nsplit,
+                           s, h_s);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_gersh_cols, dim3((unsigned)nb), dim3(kColThreads), 0, st, H, n, ldh,
                        (const double*)partial, (int)nsplit, part2, (int)nb);
-    hipLaunchKernelGGL(k_gersh_final, dim3(1), dim3(kFinalThreads), 0, st, (const double*)part2, (int)nb, s);
+    hipLaunchKernelGGL(k_gersh_final, dim3(1), dim3(kFinalThreads), 0, st, (const double*)part2, (int)nb, s,
+                       h_s);
     return hipGetLastError();
 }
 
@@ -212,10 +255,6 @@ hipError_t launch_traces(const void* base, int64_t stride, int count, int64_t n,
         hipLaunchKernelGGL(k_traces<float>, dim3(count), dim3(256), 0, st, (const float*)base,
                            stride, n, ld, out);
     return hipGetLastError();
-}
-
-hipError_t launch_trace_f64(const double* D, int64_t n, int64_t ld, double* out, hipStream_t st) {
-    return launch_traces(D, 0, 1, n, ld, 1, out, st);
 }
 
 }  // namespace chebdm

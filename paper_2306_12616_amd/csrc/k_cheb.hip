@@ -51,33 +51,81 @@ k_fermi_table(int64_t M, const DevScalars* __restrict__ s, double* __restrict__ 
     f[j] = fermi_scaled(x, s->beta_s, s->mu_s);
 }
 
-// One workgroup per coefficient n: c_n = (2 - delta_{n0})/M sum_j f_j cos(n theta_j).
+// Cosines along an arithmetic sequence of angles: an exactly reduced sincospi every kTurn terms and
+// plane rotations between, within kTurn ulp of 1.  A cospi per term bound these transforms
+// (M (L + 1) of them).  c_n against long double sums, order 512, M = 16384: at most 2.2e-17 off, 3.9e-18
+// rms (with a cospi per term 1.9e-17 and 3.3e-18, with eight terms a turn 2.5e-17 and 4.8e-18 for
+// 1 us less).
+constexpr int kTurn = 4;
+
+__device__ __forceinline__ void node_sincos(int64_t q, int64_t M, double& s, double& c) {
+    sincospi((double)q / (double)(2 * M), &s, &c);
+}
+
+// One workgroup per coefficient n: c_n = (2 - delta_{n0})/M sum_j f_j cos(n theta_j).  Nodes j and
+// M-1-j are mirror images: cos(n theta_{M-1-j}) = (-1)^n cos(n theta_j).  Order 512, M = 16384:
+// 30 us with a cospi per node, 11 us now.
 __global__ void __launch_bounds__(256)
 k_dct2(int64_t M, const double* __restrict__ f, double* __restrict__ c, int order, int damping) {
     __shared__ double smem[4];
     const int64_t n = blockIdx.x;
-    const int64_t mod = 4 * M;
+    const int64_t mod = 4 * M, half = M / 2;
     // q_j = n (2j+1) mod 4M, advanced by 2n*256 per stride without a 64-bit divide
-    const int64_t step = (512 * n) % mod;
+    const int64_t step = (512 * n) % mod, turn = (kTurn * step) % mod;
     int64_t q = (n * (2 * (int64_t)threadIdx.x + 1)) % mod;
+    double ds, dc;
+    node_sincos(step, M, ds, dc);
+    const double sign = n % 2 ? -1.0 : 1.0;
     double acc = 0.0;
-    for (int64_t j = threadIdx.x; j < M; j += 256) {
-        acc += f[j] * node_cos(q, M);
-        q += step;
+    for (int64_t j0 = threadIdx.x; j0 < half; j0 += 256 * kTurn) {
+        double g[kTurn], cs, sn;
+#pragma unroll
+        for (int u = 0; u < kTurn; ++u) {
+            const int64_t j = j0 + 256 * u, jc = j < half ? j : half - 1;
+            const double v = fma(sign, f[M - 1 - jc], f[jc]);
+            g[u] = j < half ? v : 0.0;
+        }
+        node_sincos(q, M, sn, cs);
+#pragma unroll
+        for (int u = 0; u < kTurn; ++u) {
+            acc = fma(g[u], cs, acc);
+            const double t = fma(cs, dc, -sn * ds);
+            sn = fma(sn, dc, cs * ds);
+            cs = t;
+        }
+        q += turn;
         if (q >= mod) q -= mod;
     }
+    if (M % 2 && threadIdx.x == 0) acc = fma(f[half], node_cos((n * M) % mod, M), acc);   // the node x = 0
     acc = block_sum<256>(acc, smem);
     if (threadIdx.x == 0) c[n] = (n == 0 ? 1.0 : 2.0) * acc / (double)M * damping_factor(damping, (int)n, order);
 }
 
-// Block coefficients, one workgroup.  Output coef[l*k + i] = weight of T_i in block l.
+// Two Clenshaw chains for the giant steps: with T_{h+j} = 2 T_h T_j - T_{h-j} (eq. "identity"
+// with a = h, b = j), sum_{l<m} T_l(Y) R_l = sum_{l<h} T_l(Y) R''_l + T_h(Y) sum_{j<m-h} T_j(Y) R'_j,
+// R'_0 = R_h, R'_j = 2 R_{h+j}, R''_{h-j} = R_{h-j} - R_{h+j} (1 <= j < m - h <= h).  Applied to
+// column i of the blocks base .. base + m - 1 in place: block h + j then holds R'_j.
+__device__ inline void split_column(double (*d)[kMaxBlocks], int i, int base, int m, int h) {
+    for (int j = 1; h + j < m; ++j) {
+        const double up = d[base + h + j][i];
+        d[base + h - j][i] -= up;
+        d[base + h + j][i] = 2.0 * up;
+    }
+}
+
+// Block coefficients, one workgroup.  Output coef[l*k + i] = weight of T_i in block l.  The
+// coefficients are staged in LDS first: the recurrence over l is then a chain of LDS reads.
+// split_h, split_q > 0: blocks rearranged for two and four Clenshaw chains.
 __global__ void __launch_bounds__(64)
 k_block_coeffs(const double* __restrict__ c, int order, int k, int m, int form,
-               double* __restrict__ coef) {
+               double* __restrict__ coef, int split_h, int split_q) {
     __shared__ double a[kMaxBlocks][kMaxBlocks];   // a[j][l] of T_k^j = sum_l a_{j,l} T_{lk}
     __shared__ double d[kMaxBlocks][kMaxBlocks];   // d[l][i]: block l, index i (output layout)
+    __shared__ double cl[kMaxBlocks * kMaxBlocks];
     const int tid = threadIdx.x;
-    auto cpad = [&](int idx) -> double { return idx <= order ? c[idx] : 0.0; };
+    for (int i = tid; i < k * m; i += 64) cl[i] = i <= order ? c[i] : 0.0;
+    __syncthreads();
+    auto cpad = [&](int idx) -> double { return cl[idx]; };
 
     if (form == CHEBDM_GIANT_COMPOSITION) {
         // e_{l,0} = c_{lk}; e_{l,i} = 2 c_{lk+i} - e_{l+1,k-i} (l >= 1); e_{0,i} = c_i - e_{1,k-i}/2
@@ -142,78 +190,247 @@ k_block_coeffs(const double* __restrict__ c, int order, int k, int m, int form,
             __syncthreads();
         }
     }
+    if (tid < k) {   // columns are independent
+        if (split_h > 0) split_column(d, tid, 0, m, split_h);
+        if (split_q > 0) {
+            split_column(d, tid, 0, split_h, split_q);
+            split_column(d, tid, split_h, m - split_h, split_q);
+        }
+    }
+    __syncthreads();
     for (int idx = tid; idx < k * m; idx += blockDim.x) coef[idx] = d[idx / k][idx % k];
 }
 
-// tau_0 = n, tau_i = tr T_i (i <= k), tau_{lk+i} = 2 <T_{lk}, T_i> - tau_{lk-i}.
-__global__ void __launch_bounds__(64)
+// tau_0 = n, tau_i = tr T_i (i <= k), tau_{lk+i} = 2 <T_{lk}, T_i> - tau_{lk-i}.  The recurrence over l
+// runs in LDS (through memory it took 12 us at order 512).
+__global__ void __launch_bounds__(256)
 k_assemble_moments(const double* __restrict__ tr_baby, const double* __restrict__ gram, int k, int m,
                    int order, int64_t n, double* __restrict__ tau) {
+    __shared__ double t[kMaxBlocks * kMaxBlocks + kMaxBlocks + 1];   // tau up to m k
     const int tid = threadIdx.x;
-    if (tid == 0) tau[0] = (double)n;
-    for (int i = 1 + tid; i <= k && i <= order; i += blockDim.x) tau[i] = tr_baby[i - 1];
+    if (tid == 0) t[0] = (double)n;
+    for (int i = 1 + tid; i <= k; i += 256) t[i] = tr_baby[i - 1];
+    for (int i = tid; i < (m - 1) * k; i += 256) t[k + 1 + i] = k + 1 + i <= order ? gram[i] : 0.0;   // <T_{lk}, T_i>
     __syncthreads();
-    for (int l = 1; l < m; ++l) {
-        for (int i = 1 + tid; i <= k; i += blockDim.x) {
-            const int idx = l * k + i;
-            if (idx <= order) tau[idx] = 2.0 * gram[(l - 1) * k + (i - 1)] - tau[l * k - i];
+    if (tid < 64) {   // one wavefront: its LDS accesses are in order
+        for (int l = 1; l < m; ++l) {
+            const int i = 1 + tid, idx = l * k + i;
+            const double v = i <= k && idx <= order ? 2.0 * t[idx] - t[l * k - i] : 0.0;
+            __builtin_amdgcn_wave_barrier();
+            if (i <= k) t[idx] = v;
+            __builtin_amdgcn_wave_barrier();
         }
-        __syncthreads();
     }
+    __syncthreads();
+    for (int i = tid; i <= order; i += 256) tau[i] = t[i];
 }
 
-// w_j = sum_n (2 - delta_{n0}) tau_n cos(n theta_j); also stores x_j.  kDctSplit neighbouring
-// lanes share node j, lane s summing n = s, s + kDctSplit, ...; the partial sums combine by two
-// shuffles in a fixed order.  64 nodes per work-group.
+// w_j = sum_n (2 - delta_{n0}) tau_n cos(n theta_j) at the nodes j and M-1-j (the even n add up, the
+// odd ones change sign); also stores x_j.  kDctSplit neighbouring lanes share a pair of nodes, lane s
+// summing n = s, s + kDctSplit, ...; 64 pairs per work-group.  Order 512, M = 16384: 33 us with a
+// cospi per node and term, 13 us now.
 constexpr int kDctSplit = 4;
 
 __global__ void __launch_bounds__(256)
 k_dct3(const double* __restrict__ tau, int order, int64_t M, double* __restrict__ w,
        double* __restrict__ x_tab, int damping) {
     static_assert(kDctSplit == 4, "two shuffle steps");
-    extern __shared__ double st[];
+    extern __shared__ double st[];   // (2 - delta_{n0}) tau_n, zero up to a whole turn of every lane
+    const int padded = (order / (kDctSplit * kTurn) + 1) * kDctSplit * kTurn;
     // with damping, t(mu~) = sum_n g_n c_n(mu~) tau_n: the factors go onto the moments
-    for (int i = threadIdx.x; i <= order; i += 256) st[i] = tau[i] * damping_factor(damping, i, order);
+    for (int i = threadIdx.x; i < padded; i += 256)
+        st[i] = i <= order ? (i == 0 ? 1.0 : 2.0) * (tau[i] * damping_factor(damping, i, order)) : 0.0;
     __syncthreads();
     const int s = threadIdx.x % kDctSplit;
     const int64_t j = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kDctSplit;
-    const bool live = j < M;   // no early exit: every lane takes part in the shuffles
-    const int64_t mod = 4 * M, q1 = 2 * j + 1, step = (kDctSplit * q1) % mod;
+    const bool live = j < (M + 1) / 2;   // no early exit: every lane takes part in the shuffles
+    const int64_t mod = 4 * M, q1 = 2 * j + 1, step = (kDctSplit * q1) % mod, turn = (kTurn * step) % mod;
     double acc = 0.0;
     if (live) {
+        double ds, dc;
+        node_sincos(step, M, ds, dc);
         int64_t q = (s * q1) % mod;   // n q1 mod 4M for n = s
-        for (int nn = s; nn <= order; nn += kDctSplit) {
-            acc += nn == 0 ? st[0] : 2.0 * st[nn] * node_cos(q, M);
-            q += step;
+        for (int nn = s; nn <= order; nn += kDctSplit * kTurn) {
+            double cs, sn;
+            node_sincos(q, M, sn, cs);
+#pragma unroll
+            for (int u = 0; u < kTurn; ++u) {
+                acc = fma(st[nn + kDctSplit * u], cs, acc);
+                const double t = fma(cs, dc, -sn * ds);
+                sn = fma(sn, dc, cs * ds);
+                cs = t;
+            }
+            q += turn;
             if (q >= mod) q -= mod;
         }
     }
-    acc += __shfl_xor(acc, 1, 64);
-    acc += __shfl_xor(acc, 2, 64);
+    acc += __shfl_xor(acc, 2, 64);                   // lanes 0, 2: the even n; lanes 1, 3: the odd ones
+    const double other = __shfl_xor(acc, 1, 64);
     if (live && s == 0) {
-        w[j] = acc;
-        x_tab[j] = node_cos(q1, M);
+        const double xj = node_cos(q1, M);
+        w[j] = acc + other;
+        x_tab[j] = xj;
+        if (M - 1 - j != j) {
+            w[M - 1 - j] = acc - other;
+            x_tab[M - 1 - j] = -xj;
+        }
     }
 }
 
 constexpr int kBisectThreads = 1024;
-// Bisection steps per multi-point pass of the single-problem search (seven points side by side,
-// two wavefronts each).  Measured search time (DCT-III + search) at N = 256 / 1000 / 2000,
-// float64: one step per pass 0.149 / 0.182 / 0.173 ms; two 0.126 / 0.157 / 0.151; three 0.104 /
-// 0.137 / 0.131; four 0.109 / 0.142 / 0.134; mu, trace and D bit for bit the same in every case.
+// Bisection steps per multi-point pass of one work-group (seven points side by side, two wavefronts
+// each), for the steps that the launches below leave over.
 constexpr int kBisectLevels = 3;
 
-// mu search of one problem (modes 0 bisection / 1 safeguarded Newton, search_dev.h); scratch:
-// M doubles for the tail sums
+// The search of one problem by one work-group (mode 1, safeguarded Newton); scratch: M doubles for
+// the tail sums
 __global__ void __launch_bounds__(kBisectThreads)
-k_bisect(const double* __restrict__ w, const double* __restrict__ x, int64_t M, DevScalars* s, int mode,
-         double* __restrict__ scratch) {
+k_search_newton(const double* __restrict__ w, const double* __restrict__ x, int64_t M, DevScalars* s,
+                double* __restrict__ scratch) {
     constexpr int NP = (1 << kBisectLevels) - 1;
     __shared__ double smem[kBisectThreads / 64];
     __shared__ double part[kBisectThreads / 64];
     __shared__ double win[4 * NP];
     __shared__ double tout[NP];
-    mu_search_one<kBisectThreads, kBisectLevels>(M, w, x, *s, mode, 0.0, 0.0, smem, scratch, part, win, tout);
+    mu_search_one<kBisectThreads, kBisectLevels>(M, w, x, *s, 1, 0.0, 0.0, smem, scratch, part, win, tout);
+}
+
+// Bisection (mode 0) over the whole chip.  The midpoints that the next kTreeLevels steps can visit
+// form a tree of 2^kTreeLevels - 1 points; one launch evaluates all of them, two wavefronts a point,
+// and the next launch (every work-group for itself, from the same values) takes the steps with the
+// stopping rule after each, so brackets, step count and the returned mu are those of one step at
+// a time.  A pass of one work-group over seven points took 5 us for three steps (tail sums and 16
+// passes: 94 us at N = 256, 99 at N = 1000); a launch takes 7 us for eight (whole search 55 us; with
+// ten steps a launch, 1023 points, 62).
+constexpr int kTreeLevels = 8, kTreePoints = (1 << kTreeLevels) - 1, kTreePasses = 6, kTreeNT = 128;
+
+struct SearchState {
+    double lo, hi, mid, t_mid;
+    int32_t it;      // the step to take next
+    int32_t iters, status;
+    int32_t stop;    // 1: search over, 2: no bracket (the scalars say so already)
+};
+static_assert(kTreePasses * (sizeof(SearchState) + sizeof(double) * 2) + 2 * sizeof(double) * kTreePoints <=
+                  sizeof(double) * kSearchWork, "search workspace");
+
+// Steps of the bisection from the values tv of one pass's tree.
+__device__ inline void take_steps(SearchState& st, const double* tv, double ne, double tol, int max_iter) {
+    if (st.stop) return;
+    int k = 0;
+#pragma unroll 1
+    for (int lev = 0; lev < kTreeLevels; ++lev) {
+        st.mid = 0.5 * (st.lo + st.hi);
+        st.t_mid = tv[k];
+        st.iters = st.it;
+        if (fabs(st.t_mid - ne) < tol) {
+            st.status = CHEBDM_OK;
+            st.stop = 1;
+            return;
+        }
+        const bool below = st.t_mid < ne;
+        if (below) st.lo = st.mid;
+        else st.hi = st.mid;
+        if (st.hi - st.lo < 4.0 * ulp_spacing(st.mid) || ++st.it > max_iter) {
+            st.stop = 1;
+            return;
+        }
+        k = 2 * k + (below ? 2 : 1);
+    }
+}
+
+__global__ void __launch_bounds__(kBisectThreads)
+k_search_begin(const double* __restrict__ w, const double* __restrict__ x, int64_t M, DevScalars* s,
+               double* __restrict__ scratch, SearchState* states) {
+    __shared__ double part[kBisectThreads / 64];
+    __shared__ double win[8];
+    __shared__ double tout[2];
+    const double* blk = nullptr;
+    if (M >= 4 * kQBlock) {
+        tail_sums<kBisectThreads>(w, M, scratch);
+        blk = scratch;
+    }
+    trace_pass_groups<kBisectThreads, 2>(threadIdx.x == 0 ? -1.0 : 1.0, w, x, M, s->beta_s, part, win, tout, blk);
+    if (threadIdx.x != 0) return;
+    SearchState st{-1.0, 1.0, 0.0, NAN, 1, 0, CHEBDM_WARN_NOCONV, s->max_iter < 1 ? 1 : 0};
+    if (!(tout[0] < s->n_elec && s->n_elec < tout[1])) {
+        s->mu_s = NAN;
+        s->trace = NAN;
+        s->iters = 0;
+        s->evals = 2;
+        s->learned = 0;
+        s->status = CHEBDM_ERR_BRACKET;
+        s->lo = -1.0;
+        s->hi = 1.0;
+        st.stop = 2;
+    }
+    states[0] = st;
+}
+
+// Pass p: the state before it follows from states[p - 1] and that pass's values.
+__global__ void __launch_bounds__(kTreeNT)
+k_search_pass(const double* __restrict__ w, const double* __restrict__ x, int64_t M, const DevScalars* __restrict__ s,
+              const double* __restrict__ blk, SearchState* states, double* tv, int p) {
+    __shared__ double part[kTreeNT / 64], win[4], tout[1];
+    __shared__ double prev[kTreePoints];
+    __shared__ SearchState now;
+    if (p > 0) {
+        const double* tp = tv + ((p - 1) & 1) * kTreePoints;
+        for (int i = threadIdx.x; i < kTreePoints; i += kTreeNT) prev[i] = tp[i];
+    }
+    if (threadIdx.x == 0) now = states[p > 0 ? p - 1 : 0];
+    __syncthreads();
+    if (threadIdx.x == 0 && p > 0) {
+        take_steps(now, prev, s->n_elec, s->tol, s->max_iter);
+        if (blockIdx.x == 0) states[p] = now;
+    }
+    __syncthreads();
+    if (now.stop) return;
+    const int q1 = (int)blockIdx.x + 1;
+    double l = now.lo, h = now.hi;
+    for (int b = 30 - __clz(q1); b >= 0; --b) {   // down to node blockIdx.x of the tree
+        const double m = 0.5 * (l + h);
+        if ((q1 >> b) & 1) l = m;
+        else h = m;
+    }
+    trace_pass_groups<kTreeNT, 1>(0.5 * (l + h), w, x, M, s->beta_s, part, win, tout, M >= 4 * kQBlock ? blk : nullptr);
+    if (threadIdx.x == 0) tv[(p & 1) * kTreePoints + blockIdx.x] = tout[0];
+}
+
+// The last pass's steps, any that are still left, and the result.
+__global__ void __launch_bounds__(kBisectThreads)
+k_search_end(const double* __restrict__ w, const double* __restrict__ x, int64_t M, DevScalars* s,
+             const double* __restrict__ scratch, const SearchState* states, const double* tv) {
+    constexpr int NP = (1 << kBisectLevels) - 1;
+    __shared__ double part[kBisectThreads / 64];
+    __shared__ double win[4 * NP];
+    __shared__ double tout[NP];
+    __shared__ double prev[kTreePoints];
+    __shared__ SearchState now;
+    const double* tp = tv + ((kTreePasses - 1) & 1) * kTreePoints;
+    for (int i = threadIdx.x; i < kTreePoints; i += kBisectThreads) prev[i] = tp[i];
+    if (threadIdx.x == 0) now = states[kTreePasses - 1];
+    __syncthreads();
+    const double ne = s->n_elec, tol = s->tol;
+    const int max_iter = s->max_iter;
+    if (threadIdx.x == 0) take_steps(now, prev, ne, tol, max_iter);
+    __syncthreads();
+    if (now.stop == 2) return;
+    double lo = now.lo, hi = now.hi, mid = now.mid, t_mid = now.t_mid;
+    int iters = now.iters, status = now.status;
+    if (!now.stop)
+        bisect_levels<kBisectThreads, kBisectLevels>(M, w, x, s->beta_s, ne, tol, max_iter, part, win, tout,
+                                                     M >= 4 * kQBlock ? scratch : nullptr, lo, hi, mid, t_mid, iters,
+                                                     status, now.it);
+    if (threadIdx.x == 0) {
+        s->mu_s = mid;
+        s->trace = t_mid;
+        s->iters = iters;
+        s->evals = 2 + iters;
+        s->learned = 0;
+        s->status = status;
+        s->lo = lo;
+        s->hi = hi;
+    }
 }
 
 }  // namespace
@@ -235,54 +452,46 @@ hipError_t launch_fermi_coeffs(int order, int M, const DevScalars* s, double* f_
     return hipGetLastError();
 }
 
-// Two Clenshaw chains for the giant steps: with T_{h+j} = 2 T_h T_j - T_{h-j} (eq. "identity"
-// with a = h, b = j), sum_{l<m} T_l(Y) R_l = sum_{l<h} T_l(Y) R''_l + T_h(Y) sum_{j<m-h} T_j(Y) R'_j,
-// R'_0 = R_h, R'_j = 2 R_{h+j}, R''_{h-j} = R_{h-j} - R_{h+j} (1 <= j < m - h <= h).  Applied to
-// the block coefficients in place: block h + j then holds R'_j.
-namespace {
-__global__ void k_split_blocks(double* __restrict__ coef, int k, int m, int h) {
-    const int i = threadIdx.x;
-    if (i >= k) return;
-    for (int j = 1; h + j < m; ++j) {
-        const double up = coef[(h + j) * k + i];
-        coef[(h - j) * k + i] -= up;
-        coef[(h + j) * k + i] = 2.0 * up;
-    }
-}
-}  // namespace
-
-hipError_t launch_split_blocks(double* coef, int k, int m, int h, hipStream_t st) {
-    if (k > kMaxBlocks || m > kMaxBlocks || h < 1 || m - h > h) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_split_blocks, dim3(1), dim3(64), 0, st, coef, k, m, h);
-    return hipGetLastError();
-}
-
 hipError_t launch_block_coeffs(const double* c, int order, int k, int m, int form, double* coef,
-                               hipStream_t st) {
+                               hipStream_t st, int split_h, int split_q) {
     if (k > kMaxBlocks || m > kMaxBlocks) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_block_coeffs, dim3(1), dim3(64), 0, st, c, order, k, m, form, coef);
+    if (split_h < 0 || m - split_h > (split_h ? split_h : m) || (split_q > 0 && split_h - split_q > split_q))
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_block_coeffs, dim3(1), dim3(64), 0, st, c, order, k, m, form, coef, split_h, split_q);
     return hipGetLastError();
 }
 
 hipError_t launch_assemble_moments(const double* tr_baby, const double* gram, int k, int m,
                                    int order, int64_t n, double* tau, hipStream_t st) {
-    hipLaunchKernelGGL(k_assemble_moments, dim3(1), dim3(64), 0, st, tr_baby, gram, k, m, order, n, tau);
+    hipLaunchKernelGGL(k_assemble_moments, dim3(1), dim3(256), 0, st, tr_baby, gram, k, m, order, n, tau);
     return hipGetLastError();
 }
 
 hipError_t launch_dct3(const double* tau, int order, int M, double* w, double* x_tab,
                        hipStream_t st, int damping) {
-    const size_t shmem = sizeof(double) * (size_t)(order + 1);
-    const int64_t threads = (int64_t)M * kDctSplit;
+    const size_t shmem = sizeof(double) * (size_t)(order / (kDctSplit * kTurn) + 1) * kDctSplit * kTurn;
+    const int64_t threads = ((int64_t)M + 1) / 2 * kDctSplit;
     hipLaunchKernelGGL(k_dct3, dim3((unsigned)((threads + 255) / 256)), dim3(256), shmem, st, tau, order,
                        (int64_t)M, w, x_tab, damping);
     return hipGetLastError();
 }
 
 hipError_t launch_bisect(const double* w, const double* x_tab, int M, DevScalars* s, int mode, double* scratch,
-                         hipStream_t st) {
+                         double* work, hipStream_t st) {
     if (mode < 0 || mode > 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_bisect, dim3(1), dim3(kBisectThreads), 0, st, w, x_tab, (int64_t)M, s, mode, scratch);
+    const int64_t m = M;
+    if (mode == 1) {
+        hipLaunchKernelGGL(k_search_newton, dim3(1), dim3(kBisectThreads), 0, st, w, x_tab, m, s, scratch);
+        return hipGetLastError();
+    }
+    double* tv = work;
+    SearchState* states = reinterpret_cast<SearchState*>(work + 2 * kTreePoints);
+    hipLaunchKernelGGL(k_search_begin, dim3(1), dim3(kBisectThreads), 0, st, w, x_tab, m, s, scratch, states);
+    for (int p = 0; p < kTreePasses; ++p)
+        hipLaunchKernelGGL(k_search_pass, dim3(kTreePoints), dim3(kTreeNT), 0, st, w, x_tab, m, (const DevScalars*)s,
+                           (const double*)scratch, states, tv, p);
+    hipLaunchKernelGGL(k_search_end, dim3(1), dim3(kBisectThreads), 0, st, w, x_tab, m, s, (const double*)scratch,
+                       (const SearchState*)states, (const double*)tv);
     return hipGetLastError();
 }
 

@@ -206,7 +206,15 @@ k_gram_final(const double* __restrict__ partial, int nblocks, int nl, int nt, do
     if (idx >= nl * nt) return;   // whole wavefronts leave together
     const int l = idx / nt, i = idx % nt;
     double s = 0.0;
-    for (int b = lane; b < nblocks; b += 64) s += partial[(int64_t)b * kGramMax * kGramMax + l * kGramMax + i];
+    const double* p = partial + l * kGramMax + i;
+    for (int b0 = lane; b0 < nblocks; b0 += 1024) {   // sixteen loads in flight, added in order
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            v[u] = p[(int64_t)(b0 + 64 * u < nblocks ? b0 + 64 * u : nblocks - 1) * kGramMax * kGramMax];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) s += b0 + 64 * u < nblocks ? v[u] : 0.0;
+    }
     s = wave_sum(s);
     if (lane == 0) G[idx] = s;
 }

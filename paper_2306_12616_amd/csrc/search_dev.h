@@ -76,7 +76,9 @@ __device__ void tail_sums(const double* __restrict__ w, int64_t M, double* __res
     __syncthreads();
     if (threadIdx.x == 0) {
         double s = 0.0;
-        for (int i = NT - 1; i >= 0; --i) {
+        const int used = nb < (int64_t)NT * C ? (int)((nb + C - 1) / C) : NT;   // the others hold zero
+#pragma unroll 4
+        for (int i = used - 1; i >= 0; --i) {
             const double v = chunk[i];
             chunk[i] = s;   // sum over the chunks after i
             s += v;
@@ -228,10 +230,10 @@ template <int NT, int LV>
 __device__ void bisect_levels(int64_t M, const double* __restrict__ w, const double* __restrict__ x, double beta_s,
                               double ne, double tol, int max_iter, double* part, double* win, double* tout,
                               const double* __restrict__ blk, double& lo, double& hi, double& mid, double& t_mid,
-                              int& iters, int& status) {
+                              int& iters, int& status, int it0 = 1) {
     constexpr int NP = (1 << LV) - 1;
-    int it = 1;
-    bool stop = max_iter < 1;
+    int it = it0;   // the step to take next
+    bool stop = max_iter < it0;
     while (!stop) {
         const double root = 0.5 * (lo + hi);
         int64_t j0 = 0, j1 = M;
