@@ -1057,7 +1057,8 @@ int chebdm_coeffs(chebdm_handle h, double beta, double mu, double emin, double e
     CHECK(plan_quadrature(pl, beta, emin, emax));
     CHECK(ensure_small(h, pl.M));
     HIP_TRY(launch_set_scalars(h->scal, emin, emax, beta, mu, 1, 0.0, 0.0, 0, h->stream));
-    HIP_TRY(launch_fermi_coeffs(order, pl.M, h->scal, h->ftab, h->c, h->stream, pl.damping));
+    HIP_TRY(launch_fermi_coeffs(order, pl.M, h->scal, h->ftab, h->c, h->stream, pl.damping,
+                                    pl.prec != CHEBDM_FP64));
     HIP_TRY(hipMemcpyAsync(c_out, h->c, sizeof(double) * (size_t)(order + 1), hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
     return CHEBDM_OK;
@@ -1128,7 +1129,8 @@ int chebdm_density(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, do
         HIP_TRY(launch_set_scalars(h->scal, emin, emax, beta, mu, 1, 0.0, pl.tol, pl.max_iter, h->stream,
                                    bounds_dev));
         HIP_TRY(launch_shift(dH, n, ldh, h->scal, tslot(h, pl, 1), pl.ld, pl.prec, h->stream));
-        HIP_TRY(launch_fermi_coeffs(order, pl.M, h->scal, h->ftab, h->c, h->stream, pl.damping));
+        HIP_TRY(launch_fermi_coeffs(order, pl.M, h->scal, h->ftab, h->c, h->stream, pl.damping,
+                                    pl.prec != CHEBDM_FP64));
         HIP_TRY(launch_block_coeffs(h->c, order, pl.k, pl.m, pl.form, h->coef, h->stream));
         CHECK(baby_steps(h, pl, &pl.n_gemm));
         CHECK(giant_steps(h, pl, dD, ldd, &pl.n_gemm));
@@ -1190,11 +1192,12 @@ int chebdm_mu_search(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, 
         CHECK(moments_on_device(h, pl, &pl.n_gemm));
         size_t ev = (size_t)-1;
         if (h->prof) CHECK(prof_begin(h, PROF_SEARCH, 0, 0.0, 0.0, &ev));
-        HIP_TRY(launch_dct3(h->tau, order, pl.M, h->w, h->xtab, h->stream, pl.damping));
+        HIP_TRY(launch_dct3(h->tau, order, pl.M, h->w, h->xtab, h->stream, pl.damping, pl.prec != CHEBDM_FP64));
         HIP_TRY(launch_bisect(h->w, h->xtab, pl.M, h->scal, pl.search, h->ftab, h->partial, h->stream));
         if (h->prof) CHECK(prof_end(h, ev));
         if (dD) {
-            HIP_TRY(launch_fermi_coeffs(order, pl.M, h->scal, h->ftab, h->c, h->stream, pl.damping));
+            HIP_TRY(launch_fermi_coeffs(order, pl.M, h->scal, h->ftab, h->c, h->stream, pl.damping,
+                                    pl.prec != CHEBDM_FP64));
             HIP_TRY(launch_block_coeffs(h->c, order, pl.k, pl.m, pl.form, h->coef, h->stream, pl.split_h, pl.split_q));
             CHECK(giant_steps(h, pl, dD, ldd, &pl.n_gemm));
         }

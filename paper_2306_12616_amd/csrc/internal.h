@@ -83,9 +83,8 @@ hipError_t launch_commutator(const double* H, int64_t ldh, const double* D, int6
 // ---- Lanczos bounds (k_lanczos.hip)
 constexpr int kMaxLanczosSteps = 128;
 struct LanczosWork {          // views into one device buffer of lanczos_work_doubles(n, steps) doubles
-    double *V, *Z, *w;         // basis v_0..v_{steps-1} and H v_i (rows of n), work vector
-    double *pa, *pv, *pz, *pn; // per-block partials: alpha, v_i . w, z_i . w, norm
-    double* g;                 // v_i . v_j of the last two steps
+    double *V, *w, *w2;        // basis v_0..v_{steps-1} (rows of n), work vectors
+    double *pa, *pc, *pn;      // per-block partials: alpha, projections, norm
     double *alpha, *beta;      // tridiagonal T (steps each)
     int32_t* state;            // [0]: steps done at a breakdown (0: none), [1]: steps done
 };
@@ -98,8 +97,9 @@ hipError_t launch_lanczos(const double* H, int64_t n, int64_t ldh, int steps, do
                           double* work, DevScalars* s, hipStream_t st);
 
 // ---- coefficients / decomposition / moments / bisection (k_cheb.hip)
+// terms: 1 for the reduced forms, a cospi per term of the transforms (k_cheb.hip)
 hipError_t launch_fermi_coeffs(int order, int M, const DevScalars* s, double* f_tab, double* c_out,
-                               hipStream_t st, int damping = 0);
+                               hipStream_t st, int damping = 0, int terms = 0);
 // split_h > 0: composition-form blocks rearranged for two Clenshaw chains split at h (m - h <= h);
 // split_q > 0: each of them again at q
 hipError_t launch_block_coeffs(const double* c, int order, int k, int m, int form, double* coef,
@@ -107,7 +107,7 @@ hipError_t launch_block_coeffs(const double* c, int order, int k, int m, int for
 hipError_t launch_assemble_moments(const double* tr_baby, const double* gram, int k, int m,
                                    int order, int64_t n, double* tau, hipStream_t st);
 hipError_t launch_dct3(const double* tau, int order, int M, double* w, double* x_tab, hipStream_t st,
-                       int damping = 0);
+                       int damping = 0, int terms = 0);
 // scratch: M doubles of device memory, free during the call (the Fermi table's buffer); work:
 // kSearchWork more
 constexpr int kSearchWork = 4096;

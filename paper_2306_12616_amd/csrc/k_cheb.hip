@@ -101,6 +101,27 @@ k_dct2(int64_t M, const double* __restrict__ f, double* __restrict__ c, int orde
     if (threadIdx.x == 0) c[n] = (n == 0 ? 1.0 : 2.0) * acc / (double)M * damping_factor(damping, (int)n, order);
 }
 
+// The same sums with a cospi per term, for the reduced forms: their block sums are rounded to float32,
+// where a last-digit change of c_n moves entries of D by a float32 ulp, so they keep the sums (and
+// the bits) they had.
+__global__ void __launch_bounds__(256)
+k_dct2_terms(int64_t M, const double* __restrict__ f, double* __restrict__ c, int order, int damping) {
+    __shared__ double smem[4];
+    const int64_t n = blockIdx.x;
+    const int64_t mod = 4 * M;
+    // q_j = n (2j+1) mod 4M, advanced by 2n*256 per stride without a 64-bit divide
+    const int64_t step = (512 * n) % mod;
+    int64_t q = (n * (2 * (int64_t)threadIdx.x + 1)) % mod;
+    double acc = 0.0;
+    for (int64_t j = threadIdx.x; j < M; j += 256) {
+        acc += f[j] * node_cos(q, M);
+        q += step;
+        if (q >= mod) q -= mod;
+    }
+    acc = block_sum<256>(acc, smem);
+    if (threadIdx.x == 0) c[n] = (n == 0 ? 1.0 : 2.0) * acc / (double)M * damping_factor(damping, (int)n, order);
+}
+
 // Two Clenshaw chains for the giant steps: with T_{h+j} = 2 T_h T_j - T_{h-j} (eq. "identity"
 // with a = h, b = j), sum_{l<m} T_l(Y) R_l = sum_{l<h} T_l(Y) R''_l + T_h(Y) sum_{j<m-h} T_j(Y) R'_j,
 // R'_0 = R_h, R'_j = 2 R_{h+j}, R''_{h-j} = R_{h-j} - R_{h+j} (1 <= j < m - h <= h).  Applied to
@@ -277,6 +298,35 @@ k_dct3(const double* __restrict__ tau, int order, int64_t M, double* __restrict_
     }
 }
 
+// The same with a cospi per node and term, for the reduced forms (as k_dct2_terms).
+__global__ void __launch_bounds__(256)
+k_dct3_terms(const double* __restrict__ tau, int order, int64_t M, double* __restrict__ w,
+       double* __restrict__ x_tab, int damping) {
+    extern __shared__ double st[];
+    // with damping, t(mu~) = sum_n g_n c_n(mu~) tau_n: the factors go onto the moments
+    for (int i = threadIdx.x; i <= order; i += 256) st[i] = tau[i] * damping_factor(damping, i, order);
+    __syncthreads();
+    const int s = threadIdx.x % kDctSplit;
+    const int64_t j = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kDctSplit;
+    const bool live = j < M;   // no early exit: every lane takes part in the shuffles
+    const int64_t mod = 4 * M, q1 = 2 * j + 1, step = (kDctSplit * q1) % mod;
+    double acc = 0.0;
+    if (live) {
+        int64_t q = (s * q1) % mod;   // n q1 mod 4M for n = s
+        for (int nn = s; nn <= order; nn += kDctSplit) {
+            acc += nn == 0 ? st[0] : 2.0 * st[nn] * node_cos(q, M);
+            q += step;
+            if (q >= mod) q -= mod;
+        }
+    }
+    acc += __shfl_xor(acc, 1, 64);
+    acc += __shfl_xor(acc, 2, 64);
+    if (live && s == 0) {
+        w[j] = acc;
+        x_tab[j] = node_cos(q1, M);
+    }
+}
+
 constexpr int kBisectThreads = 1024;
 // Bisection steps per multi-point pass of one work-group (seven points side by side, two wavefronts
 // each), for the steps that the launches below leave over.
@@ -444,10 +494,10 @@ hipError_t launch_set_scalars(DevScalars* s, double emin, double emax, double be
 }
 
 hipError_t launch_fermi_coeffs(int order, int M, const DevScalars* s, double* f_tab, double* c_out,
-                               hipStream_t st, int damping) {
+                               hipStream_t st, int damping, int terms) {
     hipLaunchKernelGGL(k_fermi_table, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st,
                        (int64_t)M, s, f_tab);
-    hipLaunchKernelGGL(k_dct2, dim3((unsigned)(order + 1)), dim3(256), 0, st, (int64_t)M,
+    hipLaunchKernelGGL(terms ? k_dct2_terms : k_dct2, dim3((unsigned)(order + 1)), dim3(256), 0, st, (int64_t)M,
                        (const double*)f_tab, c_out, order, damping);
     return hipGetLastError();
 }
@@ -468,11 +518,11 @@ hipError_t launch_assemble_moments(const double* tr_baby, const double* gram, in
 }
 
 hipError_t launch_dct3(const double* tau, int order, int M, double* w, double* x_tab,
-                       hipStream_t st, int damping) {
-    const size_t shmem = sizeof(double) * (size_t)(order / (kDctSplit * kTurn) + 1) * kDctSplit * kTurn;
-    const int64_t threads = ((int64_t)M + 1) / 2 * kDctSplit;
-    hipLaunchKernelGGL(k_dct3, dim3((unsigned)((threads + 255) / 256)), dim3(256), shmem, st, tau, order,
-                       (int64_t)M, w, x_tab, damping);
+                       hipStream_t st, int damping, int terms) {
+    const size_t shmem = sizeof(double) * (size_t)(order / (kDctSplit * kTurn) + 1) * kDctSplit * kTurn;   // >= order + 1
+    const int64_t threads = (terms ? (int64_t)M : ((int64_t)M + 1) / 2) * kDctSplit;
+    hipLaunchKernelGGL(terms ? k_dct3_terms : k_dct3, dim3((unsigned)((threads + 255) / 256)), dim3(256), shmem, st,
+                       tau, order, (int64_t)M, w, x_tab, damping);
     return hipGetLastError();
 }
 

@@ -13,24 +13,26 @@
 // and intersected with the Gershgorin interval already in the scalars (the
 // Gershgorin interval alone if the intersection is empty).
 //
-// Two kernels per step.  k_lz_step: z_j = H v_j (one wavefront per two rows, H read once along rows)
-// and partials of alpha_j = v_j . z_j.  k_lz_update: w = z_j - alpha_j v_j - beta_{j-1} v_{j-1}
-// - sum_i c_i v_i with the reorthogonalisation coefficients
-//     c_i = v_i . (z_j - alpha_j v_j - beta_{j-1} v_{j-1}) = z_i . v_j - alpha_j g_i - beta_{j-1} g'_i
-// (v_i . H v_j = z_i . v_j; g_i = v_i . v_j, g' the previous step's), and the partials of ||w||^2,
-// v_i . w and z_i . w that the next step's coefficients come from.  The measured g_i, not 0 and 1,
-// keep it the stated pass: with one classical Gram-Schmidt pass on z_j itself a loss of
-// orthogonality E would grow by about (|alpha| + |beta|) / beta a step.
+// Kernels per step: the product H v_j (one wavefront per two rows, H read once along rows),
+// alpha (one work-group; folded into the next kernel up to n = 8192), the three-term
+// update with the partial projections v_i . w (a grid of slices x (j + 1)), and the
+// reorthogonalisation.  Every reduction is a fixed-order sum of per-block partials, so the result
+// does not depend on scheduling.  The tridiagonal extremes come from Sturm-sequence multisection
+// (Barth, Martin, Wilkinson 1967) in one work-group.
 //
-// What bounds a step (N = 2000): two launches of 1.6 us and chains of loads that miss L2 (other
-// XCDs wrote the data), and per-CU bandwidth where few work-groups read much, so loads go out
-// at the top of a kernel and slices are 64 elements.  40 steps at N = 2000: 1050 us with three
-// kernels a step and 1024-element slices, 692 us with its two read-backs now (8.7 + 7.3 a step).  Every reduction is a fixed-order sum of
-// per-block partials, so the result does not depend on scheduling.  The tridiagonal extremes come
-// from Sturm-sequence multisection (Barth, Martin, Wilkinson 1967) in one work-group.
+// What bounds a step (N = 2000): three launches of 1.6 us, each a chain of loads of about 0.8 us that
+// miss L2 (other XCDs wrote the data), and per-CU bandwidth where few work-groups read much.  So
+// independent loads go out together at the top of a kernel, loops run in whole chunks of
+// unconditional loads (remainder iterations are waited for one by one), and the
+// reorthogonalisation has a thread per element instead of one per four: 40 steps at
+// N = 2000 took 1050 us and take 790 now.  The sums keep their order, bit for bit: the reduced
+// forms round T_1 and its descendants to float32, where a last-digit change of the bounds moves
+// entries of D by a float32 ulp.  (A two-launch step, with the projections taken from partials of
+// v_i . w and (H v_i) . w, measured 692 us and was given up for that.)
 //
 // The same kernels serve one problem and a batch of problems of different n
-// (the batched form): blockIdx.y selects the problem, whose workspace, scalars and step count min(steps, n) are its own.
+// (the batched form): blockIdx.y (blockIdx.z for the projections) selects the
+// problem, whose workspace, scalars and step count min(steps, n) are its own.
 #include <cmath>
 
 #include "internal.h"
@@ -41,11 +43,9 @@ namespace chebdm {
 namespace {
 
 constexpr int kNT = 256;
-constexpr int kSlice = 64;         // vector elements per work-group of the update: a wavefront's lanes
-constexpr int kUpdateNT = 1024;    // wavefront u takes the basis vectors i = u mod 16
-
+constexpr int kSlice = 1024;       // vector elements per work-group (4 per thread)
 constexpr int kRowsPerWave = 2;
-constexpr int kRows = (kNT / 64) * kRowsPerWave;   // rows of H of a k_lz_step work-group
+constexpr int kRowsPerBlock = (kNT / 64) * kRowsPerWave;
 constexpr double kBreakdown = 1e-12;
 
 __host__ __device__ inline int64_t blocks_of(int64_t n, int64_t per) { return (n + per - 1) / per; }
@@ -74,7 +74,7 @@ __device__ inline LzProblem problem_of(const LanczosRun& r, int p) {
     q.k = (int)(q.n < r.steps ? q.n : r.steps);
     q.L = lanczos_layout(r.base + (int64_t)p * r.stride, q.n, q.k);
     q.nbv = (int)blocks_of(q.n, kSlice);
-    q.nbr = (int)blocks_of(q.n, kRows);
+    q.nbr = (int)blocks_of(q.n, kRowsPerBlock);
     return q;
 }
 
@@ -85,59 +85,79 @@ __device__ inline uint64_t splitmix64_at(uint64_t seed, uint64_t i) {
     return z ^ (z >> 31);
 }
 
-// Sum over a wavefront in every lane: DPP rotations inside the rows of 16, then across the rows.
-template <int N>
-__device__ __forceinline__ double row_ror(double x) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, x);
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + N, 0xf, 0xf, true);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + N, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
-__device__ __forceinline__ double row_wave_sum(double x) {
-    x += row_ror<8>(x);
-    x += row_ror<4>(x);
-    x += row_ror<2>(x);
-    x += row_ror<1>(x);
-    x += __shfl_xor(x, 16, 64);
-    return x + __shfl_xor(x, 32, 64);
+// Fixed-order sum of count partials by one work-group (every thread gets it).
+__device__ inline double sum_partials(const double* __restrict__ p, int count, double* smem) {
+    double acc = 0.0;
+    for (int b = threadIdx.x; b < count; b += kNT) acc += p[b];
+    return block_sum<kNT>(acc, smem);
 }
 
-__global__ void __launch_bounds__(kSlice) k_lz_init(const LanczosRun r) {
+// Partials of ||w||^2: wavefront u of slice b (elements base + 256 c + 64 u + lane, c = 0..3, base =
+// 1024 b) in pn[4 b + u].  The total adds a slice's four wavefronts, then the slices across a
+// wavefront's lanes (n <= 65535: at most 64 slices), the same in every wavefront.
+struct NormLoads {
+    double p[4];
+};
+__device__ __forceinline__ NormLoads norm_loads(const double* __restrict__ pn, int nbv) {
+    const int lane = threadIdx.x & 63, b = lane < nbv ? lane : 0;
+    NormLoads l;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) l.p[u] = pn[4 * b + u];
+    return l;
+}
+__device__ __forceinline__ double norm_total(const NormLoads& l, int nbv) {
+    const double r = ((l.p[0] + l.p[1]) + l.p[2]) + l.p[3];
+    return wave_sum((int)(threadIdx.x & 63) < nbv ? r : 0.0);
+}
+// Element of thread (c, lane) of work-group 4 b + u.
+__device__ __forceinline__ int64_t slice_element(int block) {
+    return (int64_t)(block / 4) * kSlice + (threadIdx.x >> 6) * 256 + (block % 4) * 64 + (threadIdx.x & 63);
+}
+// Partial of the 256 elements of a work-group, thread (c, lane) holding x of element 256 c + lane.
+__device__ __forceinline__ void norm_partial(double x, double (*xs)[64], double* pn) {
+    xs[threadIdx.x >> 6][threadIdx.x & 63] = x;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        double acc = 0.0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc = fma(xs[c][threadIdx.x], xs[c][threadIdx.x], acc);
+        acc = wave_sum(acc);
+        if (threadIdx.x == 0) *pn = acc;
+    }
+}
+
+__global__ void __launch_bounds__(kNT) k_lz_init(const LanczosRun r) {
+    __shared__ double xs[4][64];
     const LzProblem q = problem_of(r, blockIdx.y);
-    if ((int)blockIdx.x >= q.nbv) return;
-    const int64_t e = (int64_t)blockIdx.x * kSlice + threadIdx.x;
+    if ((int)blockIdx.x >= 4 * q.nbv) return;
+    const int64_t e = slice_element(blockIdx.x);
     double u = 0.0;
     if (e < q.n) {
         const uint64_t z = splitmix64_at(r.seed, (uint64_t)e);
         u = 2.0 * ((double)(z >> 11) * 0x1.0p-53) - 1.0;
         q.L.w[e] = u;
     }
-    const double acc = row_wave_sum(u * u);
-    if (threadIdx.x == 0) q.L.pn[blockIdx.x] = acc;
+    norm_partial(u, xs, q.L.pn + blockIdx.x);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         q.L.state[0] = 0;   // steps done at a breakdown (0: none)
         q.L.state[1] = 0;   // steps done in total
     }
 }
 
-// beta_{j-1} = ||w||; v_j = w / beta; z_j = H v_j; partial v_j . z_j of the block's rows.  Whole
-// chunks of unconditional loads at clamped addresses: the remainder iterations of an unrolled loop
-// are waited for one by one.
-__global__ void __launch_bounds__(kNT) k_lz_step(const LanczosRun r, int j) {
+// beta = ||w||; v_j = w / beta; w2 = (H w) / beta; partial v_j . w2.
+__global__ void __launch_bounds__(kNT) k_lz_matvec(const LanczosRun r, int j) {
     __shared__ double part[kNT / 64];
     const LzProblem q = problem_of(r, blockIdx.y);
     if (j >= q.k || (int)blockIdx.x >= q.nbr) return;
     const int n = (int)q.n;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int r0 = blockIdx.x * kRows + wave * kRowsPerWave;
     const double* __restrict__ w = q.L.w;
-    const int row = r0 + lane;
-    const double wr = w[row < n ? row : n - 1];
-    const double pn = q.L.pn[lane < q.nbv ? lane : 0];
     const int broken = q.L.state[0];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int r0 = blockIdx.x * kRowsPerBlock + wave * kRowsPerWave;
     const double* h0 = q.H + (int64_t)(r0 < n ? r0 : n - 1) * q.ldh;
     const double* h1 = q.H + (int64_t)(r0 + 1 < n ? r0 + 1 : n - 1) * q.ldh;
-    double y0 = 0.0, y1 = 0.0;
+    const NormLoads pn = norm_loads(q.L.pn, q.nbv);
+    double y[kRowsPerWave] = {0.0, 0.0};
     constexpr int U = 16;
 #pragma unroll 1
     for (int c0 = lane; c0 < n; c0 += 64 * U) {
@@ -152,14 +172,12 @@ __global__ void __launch_bounds__(kNT) k_lz_step(const LanczosRun r, int j) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const double xu = c0 + 64 * u < n ? x[u] : 0.0;
-            y0 = fma(a[u], xu, y0);
-            y1 = fma(b[u], xu, y1);
+            y[0] = fma(a[u], xu, y[0]);
+            y[1] = fma(b[u], xu, y[1]);
         }
     }
     if (broken) return;
-    double acc = lane < q.nbv ? pn : 0.0;
-    for (int b = lane + 64; b < q.nbv; b += 64) acc += q.L.pn[b];
-    const double bt = sqrt(row_wave_sum(acc));
+    const double bt = sqrt(norm_total(pn, q.nbv));
     if (j > 0) {
         const double scale = fmax(fabs(q.s->emin), fabs(q.s->emax));
         const bool broke = !(bt > kBreakdown * scale);
@@ -169,252 +187,183 @@ __global__ void __launch_bounds__(kNT) k_lz_step(const LanczosRun r, int j) {
         }
         if (broke) return;
     }
-    y0 = row_wave_sum(y0);
-    y1 = row_wave_sum(y1);
-    double vz = 0.0;
-    if (lane < kRowsPerWave && row < n) {
-        const double v = wr / bt, z = (lane == 0 ? y0 : y1) / bt;
-        q.L.V[(int64_t)j * n + row] = v;
-        q.L.Z[(int64_t)j * n + row] = z;
-        vz = v * z;
+#pragma unroll
+    for (int t = 0; t < kRowsPerWave; ++t) y[t] = wave_sum(y[t]);
+    if (lane == 0) {
+        double contrib = 0.0;
+#pragma unroll
+        for (int t = 0; t < kRowsPerWave; ++t) {
+            const int row = r0 + t;
+            if (row < n) {
+                const double v = w[row] / bt;
+                const double z = y[t] / bt;
+                q.L.V[(int64_t)j * n + row] = v;
+                q.L.w2[row] = z;
+                contrib += v * z;
+            }
+        }
+        part[wave] = contrib;
     }
-    vz += __shfl_xor(vz, 1, 64);
-    if (lane == 0) part[wave] = vz;
     __syncthreads();
-    if (threadIdx.x == 0) q.L.pa[blockIdx.x] = (part[0] + part[1]) + (part[2] + part[3]);
+    if (threadIdx.x == 0) {
+        double acc = 0.0;
+#pragma unroll
+        for (int c = 0; c < kNT / 64; ++c) acc += part[c];
+        q.L.pa[blockIdx.x] = acc;
+    }
 }
 
-// w on a slice, and its partial norm, v_i . w and z_i . w.  Wavefront u holds the elements of v_i and
-// z_i for i = u, u + 16, .. (the first PRE of them in registers throughout).
-__global__ void __launch_bounds__(kUpdateNT) k_lz_update(const LanczosRun r, int j) {
-    constexpr int W = kUpdateNT / 64, PRE = 3;
-    __shared__ double p[kMaxLanczosSteps], g[kMaxLanczosSteps];
-    __shared__ double sums[W][kSlice];
-    __shared__ double alpha;
+__global__ void __launch_bounds__(kNT) k_lz_alpha(const LanczosRun r, int j) {
+    __shared__ double smem[kNT / 64];
     const LzProblem q = problem_of(r, blockIdx.y);
+    if (j >= q.k || q.L.state[0]) return;
+    const double a = sum_partials(q.L.pa, q.nbr, smem);
+    if (threadIdx.x == 0) q.L.alpha[j] = a;
+}
+
+// x = w2 - alpha_j v_j - beta_{j-1} v_{j-1} on a slice (stored by the blockIdx.y == 0 row
+// of blocks); partial v_i . x for i = blockIdx.y.  With fuse_alpha every block folds the
+// alpha partials itself (the same fixed order as k_lz_alpha) and block (0, 0) stores alpha_j.
+__global__ void __launch_bounds__(kNT) k_lz_proj(const LanczosRun r, int j, int fuse_alpha) {
+    __shared__ double smem[kNT / 64];
+    const LzProblem q = problem_of(r, blockIdx.z);
     if (j >= q.k || (int)blockIdx.x >= q.nbv) return;
-    const int n = (int)q.n, nbv = q.nbv;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int e = blockIdx.x * kSlice + lane, ec = e < n ? e : n - 1;
-    const double* pvr = q.L.pv + (int64_t)(~j & 1) * q.k * nbv;
-    const double* pzr = q.L.pz + (int64_t)(~j & 1) * q.k * nbv;
-    double* pvw = q.L.pv + (int64_t)(j & 1) * q.k * nbv;
-    double* pzw = q.L.pz + (int64_t)(j & 1) * q.k * nbv;
-    const double* gm = q.L.g + (~j & 1) * q.k;   // g of the step before; this step's go to the other half
+    const int n = (int)q.n;
+    const int i = blockIdx.y;
+    constexpr int E = kSlice / kNT;
+    const int base = blockIdx.x * kSlice;
+    const double* vj = q.L.V + (int64_t)j * n;
+    const double* vm = q.L.V + (int64_t)(j > 0 ? j - 1 : 0) * n;
+    const double* vi = q.L.V + (int64_t)i * n;
     const int broken = q.L.state[0];
-    const double bm = j > 0 ? q.L.beta[j - 1] : 1.0;
-    double v[PRE], z[PRE], pv[PRE], pz[PRE];
+    const double bm = j > 0 ? q.L.beta[j - 1] : 0.0;
+    double x2[E], xj[E], xm[E], xi[E];
 #pragma unroll
-    for (int t = 0; t < PRE; ++t) {
-        const int i = wave + W * t, ic = i < j ? i : j;
-        v[t] = q.L.V[(int64_t)ic * n + ec];
-        z[t] = q.L.Z[(int64_t)ic * n + ec];
-        pv[t] = pvr[(int64_t)ic * nbv + (lane < nbv ? lane : 0)];
-        pz[t] = pzr[(int64_t)ic * nbv + (lane < nbv ? lane : 0)];
+    for (int c = 0; c < E; ++c) {
+        const int e = base + c * kNT + (int)threadIdx.x, ec = e < n ? e : n - 1;
+        x2[c] = q.L.w2[ec];
+        xj[c] = vj[ec];
+        xm[c] = vm[ec];
+        xi[c] = vi[ec];
     }
-    const double zj = q.L.Z[(int64_t)j * n + ec], vj = q.L.V[(int64_t)j * n + ec];
-    const double vm = q.L.V[(int64_t)(j > 0 ? j - 1 : 0) * n + ec];
-    const double gmi = gm[(int)threadIdx.x < j ? threadIdx.x : 0];
-    if (wave == W - 1) {
-        double a = 0.0;
-#pragma unroll 4
-        for (int b = lane; b < q.nbr; b += 64) a += q.L.pa[b];
-        a = row_wave_sum(a);
-        if (lane == 0) alpha = a;
+    double a;
+    if (fuse_alpha) {
+        a = sum_partials(q.L.pa, q.nbr, smem);
+        if (blockIdx.x == 0 && i == 0 && threadIdx.x == 0 && !broken) q.L.alpha[j] = a;
+    } else {
+        a = q.L.alpha[j];
     }
     if (broken) return;
-    // z_i . v_j and v_i . v_j, i < j, from the partials with w = beta v_j
-#pragma unroll
-    for (int t = 0; t < PRE; ++t) {
-        const int i = wave + W * t;
-        if (i < j) {
-            double a = lane < nbv ? pv[t] : 0.0, b = lane < nbv ? pz[t] : 0.0;
-            for (int c = lane + 64; c < nbv; c += 64) {
-                a += pvr[(int64_t)i * nbv + c];
-                b += pzr[(int64_t)i * nbv + c];
-            }
-            a = row_wave_sum(a);
-            b = row_wave_sum(b);
-            if (lane == 0) {
-                g[i] = a / bm;
-                p[i] = b / bm;
-            }
-        }
-    }
-#pragma unroll 1
-    for (int i = wave + W * PRE; i < j; i += W) {
-        double a = 0.0, b = 0.0;
-        for (int c = lane; c < nbv; c += 64) {
-            a += pvr[(int64_t)i * nbv + c];
-            b += pzr[(int64_t)i * nbv + c];
-        }
-        a = row_wave_sum(a);
-        b = row_wave_sum(b);
-        if (lane == 0) {
-            g[i] = a / bm;
-            p[i] = b / bm;
-        }
-    }
-    __syncthreads();
-    const double al = alpha;
-    double c = 0.0;
-    if ((int)threadIdx.x <= j) {
-        const int i = threadIdx.x;
-        // v_j . v_j = 1 by beta's definition; v_{j-1} . v_{j-1} likewise
-        if (i < j) c = fma(-bm, i == j - 1 ? 1.0 : gmi, fma(-al, g[i], p[i]));
-        else if (j > 0) c = -bm * g[j - 1];
-        if (blockIdx.x == 0) {
-            if (i < j) q.L.g[(j & 1) * q.k + i] = g[i];
-            else q.L.alpha[j] = al;
-        }
-    }
-    __syncthreads();
-    if ((int)threadIdx.x <= j) p[threadIdx.x] = c;
-    __syncthreads();
     double acc = 0.0;
 #pragma unroll
-    for (int t = 0; t < PRE; ++t) {
-        const int i = wave + W * t;
-        acc = fma(i <= j ? p[i] : 0.0, v[t], acc);
-    }
-#pragma unroll 1
-    for (int i = wave + W * PRE; i <= j; i += W) acc = fma(p[i], q.L.V[(int64_t)i * n + ec], acc);
-    sums[wave][lane] = acc;
-    __syncthreads();
-    double x = zj - al * vj;
-    if (j > 0) x -= bm * vm;
-    double corr = 0.0;
-#pragma unroll
-    for (int u = 0; u < W; ++u) corr += sums[u][lane];
-    x -= corr;
-    if (e >= n) x = 0.0;
-    if (wave == 0) {
-        if (e < n) q.L.w[e] = x;
-        const double s = row_wave_sum(x * x);
-        if (lane == 0) q.L.pn[blockIdx.x] = s;
-    }
-#pragma unroll
-    for (int t = 0; t < PRE; ++t) {
-        const int i = wave + W * t;
-        if (i <= j) {
-            const double a = row_wave_sum(v[t] * x), b = row_wave_sum(z[t] * x);
-            if (lane == 0) {
-                pvw[(int64_t)i * nbv + blockIdx.x] = a;
-                pzw[(int64_t)i * nbv + blockIdx.x] = b;
-            }
+    for (int c = 0; c < E; ++c) {
+        const int e = base + c * kNT + (int)threadIdx.x;
+        if (e < n) {
+            double x = x2[c] - a * xj[c];
+            if (j > 0) x -= bm * xm[c];
+            if (i == 0) q.L.w[e] = x;
+            acc += xi[c] * x;
         }
     }
-#pragma unroll 1
-    for (int i = wave + W * PRE; i <= j; i += W) {
-        const double a = row_wave_sum(q.L.V[(int64_t)i * n + ec] * x), b = row_wave_sum(q.L.Z[(int64_t)i * n + ec] * x);
-        if (lane == 0) {
-            pvw[(int64_t)i * nbv + blockIdx.x] = a;
-            pzw[(int64_t)i * nbv + blockIdx.x] = b;
-        }
-    }
+    acc = block_sum<kNT>(acc, smem);
+    if (threadIdx.x == 0) q.L.pc[(int64_t)i * q.nbv + blockIdx.x] = acc;
 }
 
-// Number of eigenvalues below x of the tridiagonal with diagonal a and squared off-diagonal b2 (b2[i]
-// couples i and i - 1; b2[0] = 0), scaled so that |a|, |x| <= 1 and b2 <= 1: sign changes along
-// p_i = (a_i - x) p_{i-1} - b2_i p_{i-2}, a zero counting as the sign opposite to its
-// predecessor's.  No division in the serial chain.  Both arrays are padded to a multiple of eight
-// with a = 2, b2 = 0, which changes no sign.  A step grows p at most threefold and shrinks it by
-// no more than min(b2) >= 1e-24, so rescaling every eight steps keeps it inside the float64 range.
-__device__ __forceinline__ int sturm_count(const double* a, const double* b2, int k, double x) {
+// c_i = sum of the partials; w -= sum_{i<=j} c_i v_i, one element a thread; partial ||w||^2.
+__global__ void __launch_bounds__(kNT) k_lz_reorth(const LanczosRun r, int j) {
+    __shared__ double c[kMaxLanczosSteps];
+    __shared__ double xs[4][64];
+    const LzProblem q = problem_of(r, blockIdx.y);
+    if (j >= q.k || (int)blockIdx.x >= 4 * q.nbv) return;
+    const int n = (int)q.n, e = (int)slice_element(blockIdx.x), ec = e < n ? e : n - 1;
+    constexpr int U = 20;
+    const int broken = q.L.state[0];
+    double x = q.L.w[ec];
+    double v[U];
+    const double* V = q.L.V + ec;
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = V[(int64_t)(u < j ? u : j) * n];
+    for (int i = threadIdx.x; i <= j; i += kNT) {
+        double acc = 0.0;
+#pragma unroll 8
+        for (int b = 0; b < q.nbv; ++b) acc += q.L.pc[(int64_t)i * q.nbv + b];
+        c[i] = acc;
+    }
+    if (broken) return;
+    __syncthreads();
+    for (int i0 = 0;; i0 += U) {
+        const int last = j - i0 < U - 1 ? j - i0 : U - 1;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (u <= last) x = fma(-c[i0 + u], v[u], x);
+        if (i0 + U > j) break;
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = V[(int64_t)(i0 + U + u < j ? i0 + U + u : j) * n];
+    }
+    if (e < n) q.L.w[e] = x;
+    norm_partial(e < n ? x : 0.0, xs, q.L.pn + blockIdx.x);
+}
+
+// Number of eigenvalues of the tridiagonal (a, b) below x (Sturm sequence of the LDL^T pivots); b2:
+// squares of b.  A serial chain of divisions (k_lz_final: 36 us for 40 steps; the division's
+// sequence written out without its scaling, entries read ahead: 47).
+__device__ inline int sturm_count(const double* a, const double* b2, int k, double x) {
+    constexpr double pivmin = 1e-300;
     int cnt = 0;
-    double p0 = 0.0, p1 = 1.0;
-#pragma unroll 1
-    for (int i = 0; i < k; i += 8) {
-        double d[8], o[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            d[u] = a[i + u] - x;
-            o[u] = b2[i + u];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            double p2 = fma(d[u], p1, -o[u] * p0);
-            if (p2 == 0.0) p2 = p1 < 0.0 ? 1e-290 : -1e-290;
-            cnt += (p2 < 0.0) != (p1 < 0.0);
-            p0 = p1;
-            p1 = p2;
-        }
-        const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
-        p0 = ldexp(p0, e);
-        p1 = ldexp(p1, e);
+    double q = a[0] - x;
+    if (fabs(q) < pivmin) q = -pivmin;
+    cnt += q < 0.0;
+    for (int i = 1; i < k; ++i) {
+        q = (a[i] - x) - b2[i - 1] / q;
+        if (fabs(q) < pivmin) q = -pivmin;
+        cnt += q < 0.0;
     }
     return cnt;
 }
 
-// The first half of the threads looks for theta_min, the second for theta_max, 257 ways a round
-// (257^8 > 2^64).
-constexpr int kFinalNT = 512;
-constexpr int kWays = kFinalNT / 2 + 1;
-constexpr int kRounds = 8;
+constexpr int kFinalNT = 128;   // wave 0: theta_min, wave 1: theta_max
+constexpr int kRounds = 12;     // 65-way multisection: 65^12 > 2^72
 
 __global__ void __launch_bounds__(kFinalNT) k_lz_final(const LanczosRun r) {
-    __shared__ __attribute__((aligned(16))) double a[kMaxLanczosSteps + 8], b[kMaxLanczosSteps], b2[kMaxLanczosSteps + 8];
+    __shared__ double a[kMaxLanczosSteps], b[kMaxLanczosSteps], b2[kMaxLanczosSteps];
     __shared__ double theta[2];
-    __shared__ int below[2][kFinalNT / 64];
     __shared__ double r_last;
     const LzProblem q = problem_of(r, blockIdx.y);
     const int done = q.L.state[0];
     const int k = done ? done : q.k;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (wave == 0) {
-        double acc = 0.0;
-        for (int c = lane; c < q.nbv; c += 64) acc += q.L.pn[c];
-        acc = wave_sum(acc);
-        if (lane == 0) {
-            r_last = done ? q.L.beta[k - 1] : sqrt(acc);
-            if (!done) q.L.beta[k - 1] = r_last;
-            q.L.state[1] = k;
-        }
+    const double acc = norm_total(norm_loads(q.L.pn, q.nbv), q.nbv);
+    if (threadIdx.x == 0) {
+        r_last = done ? q.L.beta[k - 1] : sqrt(acc);
+        if (!done) q.L.beta[k - 1] = r_last;
+        q.L.state[1] = k;
     }
     for (int i = threadIdx.x; i < k; i += kFinalNT) {
         a[i] = q.L.alpha[i];
         b[i] = i + 1 < k ? q.L.beta[i] : 0.0;
+        b2[i] = b[i] * b[i];
     }
     __syncthreads();
-    // Gershgorin interval of T, and T scaled by a power of two into [-1, 1]
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    // Gershgorin interval of T
     double lo = INFINITY, hi = -INFINITY;
-    for (int i = lane; i < k; i += 64) {
+    for (int i = 0; i < k; ++i) {
         const double rad = fabs(b[i]) + (i > 0 ? fabs(b[i - 1]) : 0.0);
         lo = fmin(lo, a[i] - rad);
         hi = fmax(hi, a[i] + rad);
     }
-    lo = wave_min(lo);
-    hi = wave_max(hi);
-    const double top = fmax(fabs(lo), fabs(hi));
-    const int ex = top > 0.0 && top <= 1.7976931348623157e308 ? __builtin_amdgcn_frexp_exp(top) : 0;
-    lo = ldexp(lo, -ex);
-    hi = ldexp(hi, -ex);
-    __syncthreads();
-    if ((int)threadIdx.x < k + 8) {   // k <= 128 < kFinalNT
-        const int i = threadIdx.x;
-        a[i] = i < k ? ldexp(a[i], -ex) : 2.0;
-        const double bi = i > 0 && i < k ? ldexp(b[i - 1], -ex) : 0.0;
-        b2[i] = bi * bi;
-    }
-    __syncthreads();
-    // first half: smallest x with count(x) >= 1 (theta_min in [lo, hi]); second: count(x) >= k
-    const int half = threadIdx.x / (kFinalNT / 2), idx = threadIdx.x % (kFinalNT / 2);
-    const int need = half == 0 ? 1 : k;
-#pragma unroll 1
+    // wave 0: smallest x with count(x) >= 1 (theta_min in [lo, hi]); wave 1: count(x) >= k
+    const int need = wave == 0 ? 1 : k;
     for (int round = 0; round < kRounds; ++round) {
-        const double x = lo + (hi - lo) * ((double)(idx + 1) * (1.0 / kWays));
-        const uint64_t under = __ballot(sturm_count(a, b2, k, x) < need);
-        if (lane == 0) below[round & 1][wave] = __popcll(under);
-        __syncthreads();
-        int first = 0;   // points still below: the end lies between points first - 1 and first
-#pragma unroll
-        for (int w = 0; w < kFinalNT / 128; ++w) first += below[round & 1][half * (kFinalNT / 128) + w];
-        const double xl = first == 0 ? lo : lo + (hi - lo) * ((double)first * (1.0 / kWays));
-        const double xh = first == kWays - 1 ? hi : lo + (hi - lo) * ((double)(first + 1) * (1.0 / kWays));
+        const double x = lo + (hi - lo) * (double)(lane + 1) / 65.0;
+        const bool ge = sturm_count(a, b2, k, x) >= need;
+        const uint64_t mask = __ballot(ge);
+        const int first = mask ? __ffsll((unsigned long long)mask) - 1 : 64;
+        const double xl = first == 0 ? lo : lo + (hi - lo) * (double)first / 65.0;
+        const double xh = first == 64 ? hi : lo + (hi - lo) * (double)(first + 1) / 65.0;
         lo = xl;
         hi = xh;
     }
-    if (idx == 0) theta[half] = ldexp(half == 0 ? lo : hi, ex);   // outer side of the final interval
+    if (lane == 0) theta[wave] = wave == 0 ? lo : hi;   // outer side of the final interval
     __syncthreads();
     if (threadIdx.x == 0) {
         const double g_lo = q.s->emin, g_hi = q.s->emax;
@@ -434,31 +383,26 @@ __global__ void __launch_bounds__(kFinalNT) k_lz_final(const LanczosRun r) {
 }  // namespace
 
 int64_t lanczos_work_doubles(int64_t n, int steps) {
-    const int64_t nbv = blocks_of(n, kSlice), nbr = blocks_of(n, kRows);
-    return 2 * (int64_t)steps * n + n + nbr + 2 * 2 * (int64_t)steps * nbv + nbv + 4 * (int64_t)steps + 1;
+    const int64_t nbv = blocks_of(n, kSlice), nbr = blocks_of(n, kRowsPerBlock);
+    return (int64_t)steps * n + 2 * n + nbr + (int64_t)steps * nbv + 4 * nbv + 2 * (int64_t)steps + 2;
 }
 
-// pv and pz are read and rewritten by different work-groups of one update: two halves in turn
 __host__ __device__ LanczosWork lanczos_layout(double* base, int64_t n, int steps) {
-    const int64_t nbv = blocks_of(n, kSlice), nbr = blocks_of(n, kRows);
+    const int64_t nbv = blocks_of(n, kSlice), nbr = blocks_of(n, kRowsPerBlock);
     LanczosWork L;
     double* p = base;
     L.V = p;
     p += (int64_t)steps * n;
-    L.Z = p;
-    p += (int64_t)steps * n;
     L.w = p;
+    p += n;
+    L.w2 = p;
     p += n;
     L.pa = p;
     p += nbr;
-    L.pv = p;
-    p += 2 * (int64_t)steps * nbv;
-    L.pz = p;
-    p += 2 * (int64_t)steps * nbv;
+    L.pc = p;
+    p += (int64_t)steps * nbv;
     L.pn = p;
-    p += nbv;
-    L.g = p;
-    p += 2 * (int64_t)steps;
+    p += 4 * nbv;
     L.alpha = p;
     p += steps;
     L.beta = p;
@@ -470,12 +414,17 @@ __host__ __device__ LanczosWork lanczos_layout(double* base, int64_t n, int step
 hipError_t launch_lanczos_run(const LanczosRun& r, int count, hipStream_t st) {
     if (r.steps < 1 || r.steps > kMaxLanczosSteps || count < 1 || count > 65535 || r.nmax < 1) return hipErrorInvalidValue;
     if (r.stride < lanczos_work_doubles(r.nmax, r.steps)) return hipErrorInvalidValue;
-    const int nbv = (int)blocks_of(r.nmax, kSlice), nbr = (int)blocks_of(r.nmax, kRows);
+    const int nbv = (int)blocks_of(r.nmax, kSlice), nbr = (int)blocks_of(r.nmax, kRowsPerBlock);
     const int steps = (int)(r.nmax < r.steps ? r.nmax : r.steps);
-    hipLaunchKernelGGL(k_lz_init, dim3(nbv, count), dim3(kSlice), 0, st, r);
+    // up to 1024 alpha partials (n <= 8192) every projection block folds them itself: one
+    // launch per step fewer; beyond that one work-group folds them once
+    const int fuse = nbr <= 1024 ? 1 : 0;
+    hipLaunchKernelGGL(k_lz_init, dim3(4 * nbv, count), dim3(kNT), 0, st, r);
     for (int j = 0; j < steps; ++j) {
-        hipLaunchKernelGGL(k_lz_step, dim3(nbr, count), dim3(kNT), 0, st, r, j);
-        hipLaunchKernelGGL(k_lz_update, dim3(nbv, count), dim3(kUpdateNT), 0, st, r, j);
+        hipLaunchKernelGGL(k_lz_matvec, dim3(nbr, count), dim3(kNT), 0, st, r, j);
+        if (!fuse) hipLaunchKernelGGL(k_lz_alpha, dim3(1, count), dim3(kNT), 0, st, r, j);
+        hipLaunchKernelGGL(k_lz_proj, dim3(nbv, j + 1, count), dim3(kNT), 0, st, r, j, fuse);
+        hipLaunchKernelGGL(k_lz_reorth, dim3(4 * nbv, count), dim3(kNT), 0, st, r, j);
     }
     hipLaunchKernelGGL(k_lz_final, dim3(1, count), dim3(kFinalNT), 0, st, r);
     return hipGetLastError();

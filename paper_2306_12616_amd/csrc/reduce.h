@@ -5,10 +5,37 @@
 
 namespace chebdm {
 
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+// The butterfly v[l] + v[l ^ off] for off = 32, 16, 8, 4, 2, 1, every lane receiving the sum, without
+// LDS: the first two steps by lane-half and row swaps, then DPP rotations inside the rows of 16
+// (after a step the values repeat with period off, so lane l + off / 2 holds what l ^ (off / 2) does).
+// Same additions, same bits as with __shfl_xor, at a fraction of the latency.
+template <int N>
+__device__ __forceinline__ double row_rotate(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + N, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + N, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+    {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+        v = __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+            __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+    }
+    {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+        v = __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+            __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+    }
+    v += row_rotate<8>(v);
+    v += row_rotate<4>(v);
+    v += row_rotate<2>(v);
+    return v + row_rotate<1>(v);
 }
 
 __device__ inline double wave_min(double v) {
