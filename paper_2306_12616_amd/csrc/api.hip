@@ -787,15 +787,15 @@ int moments_on_device(chebdm_handle h, const Plan& pl, int* n_gemm) {
         std::vector<const void*> lm(lmax), tm(k);
         for (int l = 1; l <= lmax; ++l) lm[l - 1] = lptr(l);
         for (int i = 1; i <= k; ++i) tm[i - 1] = tslot(h, pl, i);
-        const int64_t nelem = pl.n * pl.ld;
         size_t ev;
-        CHECK(prof_begin(h, PROF_GRAM, 0, 0.0, (double)(lmax + k) * pl.n * pl.n * pl.elem, &ev));
+        CHECK(prof_begin(h, PROF_GRAM, 0, 0.0,
+                         (double)(lmax + k) * pl.n * (pl.elem == 8 ? 0.5 * (pl.n + 16) : pl.n) * pl.elem, &ev));
         if (pl.elem == 8)
             HIP_TRY(launch_gram<double>((const double* const*)lm.data(), lmax, (const double* const*)tm.data(), k,
-                                        nelem, h->partial, kPartialDoubles, h->gram, h->stream));
+                                        pl.n, pl.ld, h->partial, kPartialDoubles, h->gram, h->stream));
         else
             HIP_TRY(launch_gram<float>((const float* const*)lm.data(), lmax, (const float* const*)tm.data(), k,
-                                       nelem, h->partial, kPartialDoubles, h->gram, h->stream));
+                                       pl.n, pl.ld, h->partial, kPartialDoubles, h->gram, h->stream));
         CHECK(prof_end(h, ev));
     }
     HIP_TRY(launch_assemble_moments(h->trb, h->gram, k, pl.m, L, pl.n, h->tau, h->stream));

@@ -119,9 +119,10 @@ hipError_t launch_bisect(const double* w, const double* x_tab, int M, DevScalars
 template <typename T>
 hipError_t launch_combine(const T* tbase, int64_t stride, int k, int m, const double* coef,
                           T* rbase, int64_t n, int64_t ld, hipStream_t st);
-// G[l][i] = <L_l, T_i> (Frobenius) for l < nl, i < nt; L_l, T_i given by pointer lists
+// G[l][i] = <L_l, T_i> (Frobenius) for l < nl, i < nt; L_l, T_i given by pointer lists,
+// n rows of ld with a zero padding; float64 matrices are symmetric (their upper triangles are read)
 template <typename T>
-hipError_t launch_gram(const T* const* lmats, int nl, const T* const* tmats, int nt, int64_t nelem,
+hipError_t launch_gram(const T* const* lmats, int nl, const T* const* tmats, int nt, int64_t n, int64_t ld,
                        double* partial, int64_t partial_cap, double* G, hipStream_t st);
 
 // ---- matrix products (k_gemm.hip)
