@@ -153,18 +153,26 @@ struct RnsGeom {                // sizes that follow from n
     bool big;                   // 256 x 128 tiles (else 128 x 128)
 };
 RnsGeom rns_geom(int64_t n);
+// Powers of two of an operand's rows: (2^(57 - e), 2^e) at p[2 step row]; null p: e = 0 for all.
+struct RnsScale {
+    const double* p;
+    int64_t step;               // 1, or 0: one pair for all rows
+};
 struct RnsProduct {             // Out = alpha A B + beta C + gamma E + delta I (C, E may be null)
     const int8_t *planes_a, *planes_b;
-    const double *scale_a, *scale_b;   // of launch_rns_split (2 rows doubles)
+    RnsScale scale_a, scale_b;
     const double *C, *E;               // ld x ld workspace matrices
     double* Out;
     int64_t ld_out;
     double alpha, beta, gamma, delta;
     int64_t vec;                       // set by the launch
 };
-// Row scales and residue planes of `count` symmetric ld x ld matrices (ld even, zero padding).
+// Row scales (scale[i]: 2 g.rows doubles) of `count` symmetric ld x ld matrices (ld even, zero
+// padding), and residue planes by given scales, which have to be above the rows' 2-norms.
+hipError_t launch_rns_scale(const RnsGeom& g, int64_t ld, const double* const* mats, double* const* scale, int count,
+                            hipStream_t st);
 hipError_t launch_rns_split(const RnsGeom& g, int64_t ld, const double* const* mats, int8_t* const* planes,
-                            double* const* scale, int count, hipStream_t st);
+                            const RnsScale* scale, int count, hipStream_t st);
 // res: count * g.res_bytes
 hipError_t launch_rns_products(const RnsGeom& g, int64_t ld, const RnsProduct* prods, int count, int8_t* res,
                                hipStream_t st);

@@ -8,7 +8,8 @@
 // the "Ozaki scheme II" (Ozaki, Uchino, Imamura, 2025); the code is written from the mathematics:
 //
 //   scale   row r of an operand (symmetric, so also column r) gets the power of two 2^e_r above its
-//           2-norm; q = rint(x 2^(57 - e_r)), so every row of q has 2-norm <= 2^57 and by
+//           2-norm (a Chebyshev matrix of a spectrum known to lie in [-1, 1] has none above 1: e_r = 0
+//           without a pass over it); q = rint(x 2^(57 - e_r)), so every row of q has 2-norm <= 2^57 and by
 //           Cauchy-Schwarz every entry of a product stays below 2^114.
 //   split   15 residue planes q mod p_m (int8), laid out as the MFMA operand fragments.
 //   gemm    one int8 product per modulus, exact in int32; the epilogue reduces mod p_m to a byte.
@@ -39,7 +40,7 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 constexpr int NM = kRnsModuli;
 constexpr int kBits = 57;
 // Pairwise coprime, product 2^116.5 (> 2^115: sums below 2^114 of either sign, with 1.5 bits to
-// spare).  Besides 256, whose residues wrap in a byte by themselves, none is above 237: the
+// spare: rows of norm 1 + rounding at e_r = 0 are far inside them).  Besides 256, whose residues wrap in a byte by themselves, none is above 237: the
 // rounded quotient of the one-step reduction in the gemm is then close enough to keep the
 // residue inside a byte up to K = 5120 (see reduce()).
 constexpr int kMod[NM] = {256, 237, 235, 233, 229, 227, 223, 221, 217, 211, 209, 199, 197, 193, 191};
@@ -161,14 +162,19 @@ __device__ __forceinline__ void tile_rc(int t, int ntr, int ntc, int& ti, int& t
 
 // ------------------------------------------------------------------------------ scale and split
 
+struct ScaleArgs {
+    const double* A[kRnsGroup];
+    double* scale[kRnsGroup];
+};
 struct SplitArgs {
     const double* A[kRnsGroup];
     int8_t* planes[kRnsGroup];
-    double* scale[kRnsGroup];   // rows x 2^(57 - e), then rows x 2^e
+    RnsScale scale[kRnsGroup];
 };
 
-// One wavefront per row: the power of two above the row's 2-norm.
-__global__ void __launch_bounds__(256) k_rns_scale(const SplitArgs a, int64_t n, int64_t ld, int64_t rows) {
+// One wavefront per row: the power of two above the row's 2-norm.  One pass over the matrix, bound
+// by its bytes (N = 2000: 5.3 us each).
+__global__ void __launch_bounds__(256) k_rns_scale(const ScaleArgs a, int64_t n, int64_t ld, int64_t rows) {
     const int64_t row = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
     const int lane = threadIdx.x % 64;
     if (row >= rows) return;
@@ -216,8 +222,8 @@ __global__ void __launch_bounds__(256) k_rns_scale(const SplitArgs a, int64_t n,
         }
     }
     if (lane == 0) {
-        a.scale[blockIdx.y][row] = up;
-        a.scale[blockIdx.y][rows + row] = down;
+        double2* o = (double2*)a.scale[blockIdx.y] + row;
+        *o = make_double2(up, down);
     }
 }
 
@@ -232,7 +238,8 @@ __global__ void __launch_bounds__(256) k_rns_split(const SplitArgs a, int64_t n,
     if (kb >= kt) return;
     const int64_t row = (int64_t)rb * 16 + lane % 16;
     const int64_t k0 = (int64_t)kb * 64 + (lane / 16) * 2;
-    const double s = a.scale[blockIdx.z][row];
+    const RnsScale sc = a.scale[blockIdx.z];
+    const double s = sc.p ? sc.p[2 * sc.step * row] : 0x1p57;
     const double* A = a.A[blockIdx.z] + row * ld + k0;
     uint32_t lo[16], hi[16];
 #pragma unroll
@@ -377,7 +384,7 @@ struct JoinArgs {
 // are added with wrap-around (mod 1); |value / P| < 1/4, so the rest cannot carry over.
 template <int BM, int BN>
 __global__ void __launch_bounds__(256)
-k_rns_join(const JoinArgs jn, int64_t n, int64_t ld, int64_t rows, int ntr, int ntc, int ntiles, const int8_t* res) {
+k_rns_join(const JoinArgs jn, int64_t n, int64_t ld, int ntr, int ntc, int ntiles, const int8_t* res) {
     constexpr int RG = BM / 64, CB = BN / 16, NB = RG * CB / 4;
     const int lane = threadIdx.x % 64;
     const RnsProduct& d = jn.d[blockIdx.y];
@@ -394,7 +401,7 @@ k_rns_join(const JoinArgs jn, int64_t n, int64_t ld, int64_t rows, int ntr, int 
     r[15] = (v4i){0, 0, 0, 0};
     const int64_t j = j0 + lane % 16;
     const bool jin = j < n;
-    const double sb = jin ? d.scale_b[rows + j] : 0.0;
+    const double sb = !jin ? 0.0 : d.scale_b.p ? d.scale_b.p[2 * d.scale_b.step * j + 1] : 1.0;
     const bool whole = i0 + 63 < j0 && i0 + 63 < n && d.vec;   // off the diagonal, aligned rows
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -428,7 +435,8 @@ k_rns_join(const JoinArgs jn, int64_t n, int64_t ld, int64_t rows, int ntr, int 
             const int64_t i = ib + x;
             o[x] = 0.0;
             if (i < n && jin) {
-                double v = d.alpha * (fma(f, kTab.p_hi, f * kTab.p_lo) * d.scale_a[rows + i] * sb);
+                const double sa = d.scale_a.p ? d.scale_a.p[2 * d.scale_a.step * i + 1] : 1.0;
+                double v = d.alpha * (fma(f, kTab.p_hi, f * kTab.p_lo) * sa * sb);
                 if (d.C) v = fma(d.beta, d.C[i * ld + j], v);
                 if (d.E) v = fma(d.gamma, d.E[i * ld + j], v);
                 if (i == j) v += d.delta;
@@ -478,8 +486,21 @@ RnsGeom rns_geom(int64_t n) {
     return g;
 }
 
+hipError_t launch_rns_scale(const RnsGeom& g, int64_t ld, const double* const* mats, double* const* scale, int count,
+                            hipStream_t st) {
+    if (count < 1 || count > kRnsGroup || ld < g.n || ld % 2 != 0) return hipErrorInvalidValue;
+    ScaleArgs a{};
+    for (int i = 0; i < count; ++i) {
+        a.A[i] = mats[i];
+        a.scale[i] = scale[i];
+    }
+    hipLaunchKernelGGL(k_rns_scale, dim3((unsigned)((g.rows + 3) / 4), (unsigned)count), dim3(256), 0, st, a, g.n, ld,
+                       g.rows);
+    return hipGetLastError();
+}
+
 hipError_t launch_rns_split(const RnsGeom& g, int64_t ld, const double* const* mats, int8_t* const* planes,
-                            double* const* scale, int count, hipStream_t st) {
+                            const RnsScale* scale, int count, hipStream_t st) {
     if (count < 1 || count > kRnsGroup || ld < g.n || ld % 2 != 0) return hipErrorInvalidValue;
     SplitArgs a{};
     for (int i = 0; i < count; ++i) {
@@ -487,8 +508,6 @@ hipError_t launch_rns_split(const RnsGeom& g, int64_t ld, const double* const* m
         a.planes[i] = planes[i];
         a.scale[i] = scale[i];
     }
-    hipLaunchKernelGGL(k_rns_scale, dim3((unsigned)((g.rows + 3) / 4), (unsigned)count), dim3(256), 0, st, a, g.n, ld,
-                       g.rows);
     hipLaunchKernelGGL(k_rns_split, dim3((unsigned)((g.kt + 3) / 4), (unsigned)(g.rows / 16), (unsigned)count),
                        dim3(256), 0, st, a, g.n, ld, g.rows, g.kt, g.plane_bytes);
     return hipGetLastError();
@@ -514,12 +533,12 @@ hipError_t launch_rns_products(const RnsGeom& g, int64_t ld, const RnsProduct* p
         if (twice) RNS_GEMM(4, 2, 4, 4, 4, true);
         else RNS_GEMM(4, 2, 4, 4, 4, false);
         hipLaunchKernelGGL((k_rns_join<256, 128>), dim3((unsigned)(g.ntiles * 8), (unsigned)count), dim3(256), 0, st, ja,
-                           g.n, ld, g.rows, g.ntr, g.ntc, g.ntiles, (const int8_t*)res);
+                           g.n, ld, g.ntr, g.ntc, g.ntiles, (const int8_t*)res);
     } else {
         if (twice) RNS_GEMM(2, 2, 4, 4, 3, true);
         else RNS_GEMM(2, 2, 4, 4, 3, false);
         hipLaunchKernelGGL((k_rns_join<128, 128>), dim3((unsigned)(g.ntiles * 4), (unsigned)count), dim3(256), 0, st, ja,
-                           g.n, ld, g.rows, g.ntr, g.ntc, g.ntiles, (const int8_t*)res);
+                           g.n, ld, g.ntr, g.ntc, g.ntiles, (const int8_t*)res);
     }
 #undef RNS_GEMM
     return hipGetLastError();

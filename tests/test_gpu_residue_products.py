@@ -73,6 +73,23 @@ def test_bounds_inside_the_spectrum(cd, handle):
         a, b = b, 2 * (lam / 0.2) * b - a
 
 
+@pytest.mark.parametrize("n", [1400, 1537])
+def test_own_bounds_need_no_row_scales(cd, handle, n):
+    # bounds computed by the call put every T_n's rows below norm 1, given ones do not: two routes.
+    # One site is alone at the middle of the bounds (a zero row in T_1), one at their end.
+    h, _, _ = synth.hamiltonian(n, "uniform", seed=8)
+    h[3, :] = h[:, 3] = h[9, :] = h[:, 9] = 0.0
+    H = torch.from_numpy(h).cuda()
+    lo, hi = cd.chebdm_bounds(handle, H)
+    h[3, 3], h[9, 9] = 0.5 * (lo + hi), hi
+    H = torch.from_numpy(h).cuda()
+    own, _ = cd.chebdm_density(handle, H, BETA, 0.1, ORDER)
+    given, _ = cd.chebdm_density(handle, H, BETA, 0.1, ORDER, emin=lo, emax=hi)
+    assert (own - given).abs().max().item() <= 2e-12
+    tau = [cd.chebdm_moments(handle, H, 60, cd.make_opts(), *b) for b in ((np.nan, np.nan), (lo, hi))]
+    assert np.max(np.abs(tau[0] - tau[1])) <= 4 * 60 ** 2 * n * np.finfo(float).eps
+
+
 def test_non_finite_rows(cd, handle):
     n = 1400
     h, _, _ = synth.hamiltonian(n, "uniform", seed=6)
