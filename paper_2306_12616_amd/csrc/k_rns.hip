@@ -291,11 +291,17 @@ __device__ __forceinline__ void copy_chunk(uint32_t lds, uint32_t voff, const vo
 // Step k waits for its own copies of stage k, passes the barrier (stage k is then complete and
 // everyone has read stage k - 1: its reads end before the wait), starts the copies of stage
 // k + S - 1 into the buffer of stage k - 1 and multiplies.  Operands come in fragment order, so
-// LDS reads are 16 contiguous bytes a lane: no bank conflicts.  Bound by the matrix pipe and, with
-// 128-tiles, by the copies through L2 (N = 4000, one product, int8 rate executed: 2.29 POP/s with
-// 128 x 128 tiles of 4 wavefronts, three work-groups a CU; 2.47 with 256 x 128 tiles of 8, two a
-// CU; the vendor library's int8 GEMM at 4096: 2.08).  Without its copies the 128-tile loop ran at
-// 3.3, without copies and LDS reads at 3.6; zero operands alone (less switching) gave 16 % on 256-tiles.
+// LDS reads are 16 contiguous bytes a lane: no bank conflicts.  A wavefront whose block lies below
+// the diagonal copies for the others and multiplies nothing (the join never reads its residues).
+// Bound by the power of the matrix units and by LDS and copy traffic together (N = 4000, one product,
+// int8 rate executed: 2.29 POP/s with 128 x 128 tiles, three work-groups a CU; the vendor library's
+// int8 GEMM at 4096: 2.08; the 128-tile loop without copies 3.3, without LDS reads too 3.6; zero
+// operands alone, which switch less, gave 16 %).  The wavefront's 64 x 128 block, against 64 x 64, reads
+// a quarter less LDS per product.  mu search and D of order 512, N = 2000 / 2500 / 3000 / 4000 / 4600:
+// 256 x 128 tiles of eight 64 x 64 wavefronts (128-tiles at 2000 and 2500) 7.23 / 12.86 / 19.1 / 39.1 /
+// 56.9 ms; of four 64 x 128 wavefronts 7.12 / 12.15 / 19.0 / 39.0 / 56.4, and without the blocks below
+// the diagonal 7.00 / 12.11 / 18.8 / 38.6 / 55.9.  Four of 128 x 64: 7.18 at 2000, 39.8 at 4000; 256 x 256
+// tiles of eight 128 x 64 7.37 and 39.7, of sixteen 64 x 64 7.31 and 38.4.
 template <int WM, int WN, int TM, int TN, int S, int OCC, bool TWICE>
 __global__ void __launch_bounds__(64 * WM * WN, OCC)
 k_rns_gemm(const GemmArgs g, int64_t plane_bytes, int kt, int ntr, int ntc, int ntiles, int8_t* res) {
@@ -324,6 +330,7 @@ k_rns_gemm(const GemmArgs g, int64_t plane_bytes, int kt, int ntr, int ntc, int 
         for (int c = 0; c < CW; ++c) copy_chunk(l + c * 1024, voff + (uint32_t)k * 1024u, src[c]);
     };
     const int wm = w % WM, wn = w / WM;
+    const bool live = (ti * WM + wm) * TM < (tj * WN + wn + 1) * TN;   // not wholly below the diagonal
     v4i acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -339,6 +346,7 @@ k_rns_gemm(const GemmArgs g, int64_t plane_bytes, int kt, int ntr, int ntc, int 
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         if (k + S - 1 < kt) issue(k + S - 1);
+        if (!live) continue;
         const char* st = lds + (k % S) * STAGE;
         v4i a[TM], b[TN];
 #pragma unroll
@@ -351,6 +359,7 @@ k_rns_gemm(const GemmArgs g, int64_t plane_bytes, int kt, int ntr, int ntc, int 
             for (int j = 0; j < TN; ++j)
                 acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b[j], acc[i][j], 0, 0, 0);
     }
+    if (!live) return;
     // Residues as bytes.  A lane holds rows 4 (l / 16) + r of column l % 16 of each 16 x 16 block;
     // four blocks down make 16 bytes: one 1 KB store per 64 x 16 block of the output.
     const float inv = kTab.inv[m];
@@ -464,12 +473,15 @@ k_rns_join(const JoinArgs jn, int64_t n, int64_t ld, int ntr, int ntc, int ntile
 
 }  // namespace
 
-// 256 x 128 tiles of 8 wavefronts from N = 3000 (N = 4000: 437 against 457 us for 128-tiles); at
-// N = 2000 their two work-groups a CU leave a nearly empty last round (72 against 65 us).
+// 256 x 128 tiles from N = 1536, where their fewer copies outweigh the coarser last round of
+// work-groups.  Order 512 with 128-tiles and with these, ms: mu search and D, N = 1400 3.36 and 3.39,
+// 1600 4.66 and 4.56, 1800 6.32 and 6.09, 2200 9.65 and 9.15, 2700 15.6 and 14.8, 4000 41.4 and 38.6;
+// fixed mu (one product a launch), N = 1400 2.88 and 3.03, 1600 3.66 and 3.68, 1800 4.69 and 4.60,
+// 2000 5.36 and 5.45, 2200 6.99 and 6.79, 2900 12.9 and 12.1.
 RnsGeom rns_geom(int64_t n) {
     RnsGeom g;
     g.n = n;
-    g.big = n >= 3000;
+    g.big = n >= 1536;
     const int64_t bm = g.big ? 256 : 128, bn = 128;
     g.rows = (n + bm - 1) / bm * bm;
     g.kt = (int)((n + 63) / 64);
@@ -530,8 +542,8 @@ hipError_t launch_rns_products(const RnsGeom& g, int64_t ld, const RnsProduct* p
     hipLaunchKernelGGL((k_rns_gemm<WM, WN, TM, TN, 3, OCC, TW>), items, dim3(64 * WM * WN), 0, st, ga, g.plane_bytes, \
                        g.kt, g.ntr, g.ntc, g.ntiles, res)
     if (g.big) {
-        if (twice) RNS_GEMM(4, 2, 4, 4, 4, true);
-        else RNS_GEMM(4, 2, 4, 4, 4, false);
+        if (twice) RNS_GEMM(4, 1, 4, 8, 2, true);
+        else RNS_GEMM(4, 1, 4, 8, 2, false);
         hipLaunchKernelGGL((k_rns_join<256, 128>), dim3((unsigned)(g.ntiles * 8), (unsigned)count), dim3(256), 0, st, ja,
                            g.n, ld, g.ntr, g.ntc, g.ntiles, (const int8_t*)res);
     } else {

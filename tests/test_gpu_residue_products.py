@@ -73,6 +73,12 @@ def test_bounds_inside_the_spectrum(cd, handle):
         a, b = b, 2 * (lam / 0.2) * b - a
 
 
+# where the 256 x 128 tiles begin, and one row, column or K step past their edges
+@pytest.mark.parametrize("n", [1535, 1536, 1537, 1663, 1665, 1793])
+def test_density_where_large_tiles_begin(cd, handle, n):
+    test_density_at_tile_edges(cd, handle, n)
+
+
 @pytest.mark.parametrize("n", [1400, 1537])
 def test_own_bounds_need_no_row_scales(cd, handle, n):
     # bounds computed by the call put every T_n's rows below norm 1, given ones do not: two routes.
