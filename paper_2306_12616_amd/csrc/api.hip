@@ -153,7 +153,16 @@ int ensure_mats(chebdm_handle h, const Plan& pl, int64_t count) {
             h->mats = nullptr;
             h->mats_bytes = 0;
         }
-        if (hipMalloc(&h->mats, bytes) != hipSuccess) {
+        hipError_t e = hipMalloc(&h->mats, bytes);
+        if (e != hipSuccess && h->rns) {   // the residue planes of earlier calls are only a faster route
+            (void)hipGetLastError();
+            HIP_TRY(hipStreamSynchronize(h->stream));
+            HIP_TRY(hipFree(h->rns));
+            h->rns = nullptr;
+            h->rns_bytes = 0;
+            e = hipMalloc(&h->mats, bytes);
+        }
+        if (e != hipSuccess) {
             h->mats = nullptr;
             (void)hipGetLastError();
             return fail(CHEBDM_ERR_OOM, "cannot allocate " + std::to_string(bytes) + " bytes of matrix workspace");
@@ -387,6 +396,12 @@ int resolve_bounds(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, do
     if (!std::isfinite(emin) || !std::isfinite(emax) || emax < emin)
         return fail(CHEBDM_ERR_ARG, "bounds must be finite with emin <= emax");
     return 0;
+}
+
+// Bounds far enough apart for their own rounding not to matter: (e - cen) / half passes 1 by some
+// 2^-52 |cen| / half, and T_n by n^2 of that (n < 2^12, at most 2^-8 here).
+bool wide_bounds(double emin, double emax) {
+    return 0.5 * (emax - emin) >= 0x1p-20 * std::fmax(std::fabs(emin), std::fabs(emax));
 }
 
 // Library's choice between one and two giant-step chains: two wherever they can be used.
@@ -1122,6 +1137,7 @@ int chebdm_density(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, do
     CHECK(set_device(h));
     pl.unit = bounds_dev && pl.bounds != CHEBDM_BOUNDS_LANCZOS;
     CHECK(resolve_bounds(h, dH, n, ldh, emin, emax, &pl));
+    pl.unit = pl.unit && wide_bounds(emin, emax);
     CHECK(ensure_small(h, 0));
     if (emax == emin) {
         // H = cI: D = f(c) I exactly (no spectrum map exists)
@@ -1179,6 +1195,7 @@ int chebdm_mu_search(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, 
     CHECK(set_device(h));
     pl.unit = bounds_dev && pl.bounds != CHEBDM_BOUNDS_LANCZOS;
     CHECK(resolve_bounds(h, dH, n, ldh, emin, emax, &pl));
+    pl.unit = pl.unit && wide_bounds(emin, emax);
     CHECK(ensure_small(h, 0));
     if (emax == emin) {
         // H = cI: tr f(c) I = n_elec fixes the occupation n_elec/n and mu in closed form
@@ -1266,6 +1283,7 @@ int chebdm_moments(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, in
     CHECK(set_device(h));
     pl.unit = (std::isnan(emin) || std::isnan(emax)) && pl.bounds != CHEBDM_BOUNDS_LANCZOS;
     CHECK(resolve_bounds(h, dH, n, ldh, emin, emax, &pl));
+    pl.unit = pl.unit && wide_bounds(emin, emax);
     if (!(emax > emin)) return fail(CHEBDM_ERR_ARG, "moments need emin < emax");
     CHECK(ensure_small(h, 0));
     pl.ld = round_up(n, 128);

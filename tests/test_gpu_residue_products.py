@@ -96,6 +96,17 @@ def test_own_bounds_need_no_row_scales(cd, handle, n):
     assert np.max(np.abs(tau[0] - tau[1])) <= 4 * 60 ** 2 * n * np.finfo(float).eps
 
 
+def test_bounds_as_close_as_their_rounding(cd, handle):
+    # half the width is a few ulps of the centre: (e - cen) / half leaves [-1, 1], T_n grows, and the call
+    # keeps the row scales that it takes for given bounds
+    n = 1400
+    H = torch.diag(torch.from_numpy(1.0 + np.arange(n) % 4 * np.finfo(float).eps)).cuda()
+    lo, hi = cd.chebdm_bounds(handle, H)
+    assert lo < hi
+    tau = [cd.chebdm_moments(handle, H, ORDER, cd.make_opts(), *b) for b in ((np.nan, np.nan), (lo, hi))]
+    assert np.array_equal(tau[0], tau[1])
+
+
 def test_non_finite_rows(cd, handle):
     n = 1400
     h, _, _ = synth.hamiltonian(n, "uniform", seed=6)
