@@ -201,14 +201,23 @@ struct RnsLayout {
     size_t bytes;
 };
 
-// Smallest N whose float64 products run on the int8 units.
-constexpr int64_t kRnsMinN = 1400;
+// Where float64 products run on the int8 units: launches of at least two products from N = 960, single
+// ones from N = 1400.  Below N = 960 the planes' extra launches cost more than the products gain, and
+// from 1025 to 1056 four products of 48-tiles (22 a side) still fit one round of the float64 units
+// while the int8 tiles have gone from eight to nine a side.  Order 512, float64 units -> this rule ->
+// all launches on the int8 units, us: mu search and D, N = 900 1498 -> - -> 1702, 980 1874 -> 1789 ->
+// 1798, 1000 1891 -> 1787 -> 1803, 1025 2024 -> - -> 2085, 1100 2530 -> 2257 -> 2209, 1300 3722 -> 3215 ->
+// 3159; fixed mu (mostly single products) 1000 1374 -> 1330 -> 1774, 1100 2132 -> 2078 -> 2090, 1300
+// 2866 -> 2686 -> 2697; with Lanczos bounds (planes with row scales) mu search 1152 3496 -> 3094 -> 3045,
+// fixed mu 1290 3424 -> 3396 -> 3517.
+constexpr int64_t kRnsMinN = 960, kRnsSingleN = 1400;
+bool rns_pays(int64_t n) { return n >= kRnsMinN && (n <= 1024 || n > 1056); }
 
 // slots == 0: float64 units.  The operand sets take at most 8 GB (12 sets up to N = 6600; below
 // three the products would convert operands over and over, and the float64 units stay).
 RnsLayout rns_layout(const Plan& pl) {
     RnsLayout l{};
-    if (pl.prec != CHEBDM_FP64 || pl.n < kRnsMinN) return l;
+    if (pl.prec != CHEBDM_FP64 || !rns_pays(pl.n)) return l;
     l.geo = rns_geom(pl.n);
     l.set_stride = l.geo.set_bytes + 2 * l.geo.rows * (int64_t)sizeof(double);
     const int64_t fit = ((int64_t)8 << 30) / l.set_stride;
@@ -533,9 +542,6 @@ struct Chain {
             if (nscale > 0) HIP_TRY(launch_rns_scale(g, pl.ld, smats, srow, nscale, h->stream));
             if (nsplit > 0) HIP_TRY(launch_rns_split(g, pl.ld, mats, planes, scale, nsplit, h->stream));
             HIP_TRY(launch_rns_products(g, pl.ld, prod, np, res, h->stream));
-            for (int i = 0; i < np; ++i)
-                for (const void*& o : h->rns_owner)
-                    if (o == b64.d[i0 + i].Out) o = nullptr;
             i0 += np;
         }
         return 0;
@@ -546,13 +552,15 @@ struct Chain {
         size_t ev;
         CHECK(prof_begin(h, PROF_GEMM, cnt, cnt * sym_product_flop(pl.n), 0.0, &ev));
         hipError_t e = hipSuccess;
-        if (pl.elem == 8 && h->rns_slots > 0) CHECK(flush_rns());
+        if (pl.elem == 8 && h->rns_slots > 0 && (cnt > 1 || pl.n >= kRnsSingleN)) CHECK(flush_rns());
         else if (pl.elem == 8 && gemm_small_pays(pl.n, cnt)) e = launch_gemm_small(b64, pl.n, pl.ld, h->stream);
         else if (pl.elem == 8) e = launch_gemm_f64(b64, pl.n, pl.ld, h->stream, h->gemm_scratch,
                                               h->gemm_scratch ? kGemmScratchBytes : 0);
         else e = launch_gemm_f32(b32, pl.n, pl.ld,
                                  pl.prec == CHEBDM_BF16X6 ? 2 : (pl.prec == CHEBDM_BF16X3 ? 1 : 0), h->stream,
                                  h->gemm_scratch, h->gemm_scratch ? kGemmScratchBytes : 0);
+        // on either units: an output's planes are no longer current
+        for (int i = 0; i < b64.count; ++i) rns_forget(h, b64.d[i].Out, static_cast<char*>(b64.d[i].Out) + 1);
         b64.count = 0;
         b32.count = 0;
         HIP_TRY(e);

@@ -79,6 +79,22 @@ def test_density_where_large_tiles_begin(cd, handle, n):
     test_density_at_tile_edges(cd, handle, n)
 
 
+# launches of several products on the int8 units, single ones on the float64 units: the first and last
+# sizes of the rule, the gap in it, four chains (order 80: 9 blocks), ladder and blocks in the same slots.
+# sum |c_n| n^2 eps <= 80^2 * 2.2e-16 * 3 = 4.3e-12
+@pytest.mark.parametrize("n", [959, 960, 1024, 1025, 1057, 1153, 1399, 1400])
+@pytest.mark.parametrize("bounds", ["gershgorin", "lanczos"])
+def test_mixed_units(cd, handle, n, bounds):
+    print(f"mixed units n={n} {bounds}", flush=True)
+    order = 80
+    h, q, lam = synth.hamiltonian(n, "uniform", seed=n)
+    H = torch.from_numpy(h).cuda()
+    for _ in range(2):   # the second call replays the first one's launches
+        mu, D, info = cd.chebdm_mu_search(handle, H, BETA, n // 2 + 0.5, order, cd.make_opts(bounds=bounds))
+        ref, _ = density(q, lam, order, BETA, mu, info["emin"], info["emax"], info["n_quad"])
+        assert np.max(np.abs(D.cpu().numpy() - ref)) <= 5e-12
+
+
 @pytest.mark.parametrize("n", [1400, 1537])
 def test_own_bounds_need_no_row_scales(cd, handle, n):
     # bounds computed by the call put every T_n's rows below norm 1, given ones do not: two routes.
