@@ -654,16 +654,26 @@ void drop_replay(chebdm_ctx::Replay& r) {
     r.key.clear();
 }
 
-// Runs body() - launches only, all on h->stream - either eagerly (launch timing on) or as a
-// graph: captured on the handle's own stream on first use, replayed on h->stream while the
-// key matches.  The replay is ordered after everything already queued on h->stream.
-// *products: the body's product count (kept with the graph for replays).
+// Runs body() - launches only, all on h->stream - either eagerly (launch timing on, or a key that
+// the last call of this kind did not have) or as a graph: captured on the handle's own stream by
+// the second call with a key, replayed on h->stream while the key matches.  The replay is ordered
+// after everything already queued on h->stream.  *products: the body's product count (kept with the
+// graph for replays).
+// A capture pays only where the call comes again: launches queue up ahead of the device anyway.  With
+// another mu or n_elec at every call, captured each time -> eager, against the replay, us: mu search and
+// D of order 128 N = 256 299 -> 229 (224), order 512 N = 1000 1909 -> 1774 (1768), N = 3001 19310 ->
+// 18879 (18882); fixed mu of order 200 N = 333 257 -> 205 (202).
 template <class Body>
 int run_replayed(chebdm_handle h, int slot, const std::vector<char>& key, int* products, Body body) {
     if (h->prof) return body();
     chebdm_ctx::Replay& r = h->replay[slot];
-    if (!r.exec || r.key != key) {
+    if (r.key != key) {
         drop_replay(r);
+        CHECK(body());
+        r.key = key;
+        return 0;
+    }
+    if (!r.exec) {
         if (!h->cap) HIP_TRY(hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking));
         HIP_TRY(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
         hipStream_t user = h->stream;
@@ -683,7 +693,6 @@ int run_replayed(chebdm_handle h, int slot, const std::vector<char>& key, int* p
             drop_replay(r);
             HIP_TRY(ei);
         }
-        r.key = key;
         r.products = *products;
     }
     *products = r.products;

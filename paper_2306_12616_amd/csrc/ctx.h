@@ -42,7 +42,7 @@ struct chebdm_ctx {
     // captured graphs of the device part of chebdm_mu_search / chebdm_density, replayed while
     // the call's arguments (and so every kernel argument) are unchanged
     struct Replay {
-        std::vector<char> key;
+        std::vector<char> key;   // the last call's; exec is null until the second call with it
         hipGraph_t graph = nullptr;
         hipGraphExec_t exec = nullptr;
         int products = 0;   // matrix products in the captured sequence
