@@ -20,7 +20,7 @@ LIB_PATH = os.path.join(HERE, "libchebdm.so")
 
 SOURCES = ["api.hip", "api_batch.hip", "api_mlp.hip", "api_noalloc.hip", "k_batch.hip", "k_bounds.hip", "k_check.hip", "k_cheb.hip", "k_combine.hip",
            "k_gemm.hip", "k_lanczos.hip", "k_mlp.hip", "k_rns.hip",
-           "k_small.hip"]
+           "k_small.hip", "k_sum.hip"]
 ARCH = os.environ.get("CHEBDM_OFFLOAD_ARCH", "gfx950")
 
 # -packed-fp32-ops: keep the compiler from forming packed FP32 VALU ops.

@@ -83,6 +83,7 @@ struct Plan {
     int chains = 0;    // composition form: 0 library's choice, 1, 2 or 4 chains
     int split_h = 0;   // > 0: giant steps as two Clenshaw chains joined by T_h(T_k) (extra slot k + m)
     int split_q = 0;   // > 0: each half split again at q, joined by T_q(T_k) (extra slot k + m + 1)
+    bool sum = false;  // D as one sum of products with the ladder (slots k .. k + m - 3, blocks after them)
     double lz_margin = 0.01;
     double tol = 1e-10;
     size_t elem = 8;
@@ -458,8 +459,20 @@ int four_chain_split(const Plan& pl, int split_h) {
     return (split_h + 1) / 2;
 }
 
-// Slots the giant-step chains keep beyond the k + m of the plan: T_h(T_k), and T_q(T_k).
-int extra_chain_slots(const Plan& pl) { return (pl.split_h > 0 ? 1 : 0) + (pl.split_q > 0 ? 1 : 0); }
+// Whether the density is one sum of products with the ladder's matrices: float64 composition form
+// where the library chooses, with a ladder up to T_{(m-1)k} (an order that k divides ends one short).
+// Up to N = 1152: past it the chains' products on the int8 units are as fast (k_sum.hip has both sides).
+constexpr int64_t kSumMaxN = 1152;
+bool sum_pays(const Plan& pl) {
+    return pl.prec == CHEBDM_FP64 && pl.form == CHEBDM_GIANT_COMPOSITION && pl.chains == 0 && pl.m >= 3 &&
+           (pl.order - 1) / pl.k >= pl.m - 1 && pl.n <= kSumMaxN;
+}
+
+// Slots kept beyond the k + m of the plan: the ladder's matrices that the sum of products reads, or
+// the giant-step chains' T_h(T_k), and T_q(T_k).
+int extra_chain_slots(const Plan& pl) {
+    return pl.sum ? pl.m - 2 : (pl.split_h > 0 ? 1 : 0) + (pl.split_q > 0 ? 1 : 0);
+}
 
 // ---------------------------------------------------------------- GEMM helper
 
@@ -571,8 +584,8 @@ struct Chain {
 
 // T_i for i >= 1 lives in slot i-1.
 void* tslot(chebdm_handle h, const Plan& pl, int i) { return slot(h, pl, i - 1); }
-// R_l lives in slot k + l.
-void* rslot(chebdm_handle h, const Plan& pl, int l) { return slot(h, pl, pl.k + l); }
+// R_l lives in slot k + l, after the ladder's m - 2 slots where those are kept.
+void* rslot(chebdm_handle h, const Plan& pl, int l) { return slot(h, pl, pl.k + (pl.sum ? pl.m - 2 : 0) + l); }
 
 // Step s of the odd-chain schedule for P_2..P_K: the odd s >= 3 with the fewest launches when
 // P_2..P_s take s - 1 one-product launches, plus ceil((K - s) / s) rounds of s; ties go to the
@@ -597,7 +610,7 @@ int odd_chain_step(int K) {
 // Everything a captured device sequence depends on: if two calls agree on all of it, every
 // kernel argument of their sequences agrees, and the first call's graph can be replayed.
 struct ReplayKey {
-    int32_t kind, order, k, m, prec, form, baby, ladder, search, max_iter, bounds_on_device, unit, damping, split_h,
+    int32_t kind, order, k, m, prec, form, baby, ladder, search, max_iter, bounds_on_device, unit, sum, damping, split_h,
         split_q;
     int64_t n, ld, ldh, ldd, M;
     const void *dH, *dD, *mats, *small, *rns;   // rns: null when the products run on the float64 units
@@ -624,6 +637,7 @@ std::vector<char> replay_key(int kind, const Plan& pl, chebdm_handle h, const do
     k.damping = pl.damping;
     k.bounds_on_device = bounds_on_device ? 1 : 0;
     k.unit = pl.unit ? 1 : 0;
+    k.sum = pl.sum ? 1 : 0;
     k.n = pl.n;
     k.ld = pl.ld;
     k.ldh = ldh;
@@ -812,7 +826,7 @@ int baby_steps(chebdm_handle h, const Plan& pl, int* n_gemm) {
     return chebyshev_powers(ch, pl, [&](int i) -> void* { return tslot(h, pl, i); }, pl.k, pl.baby);
 }
 
-// Ladder T_{2k}, ..., T_{lmax k} (T_{lk} in R slot l-2) and the moments tau_0..tau_L.
+// Ladder T_{2k}, ..., T_{lmax k} (T_{lk} in slot k + l - 2: R slot l - 2 except with a sum of products) and the moments tau_0..tau_L.
 int moments_on_device(chebdm_handle h, const Plan& pl, int* n_gemm) {
     const int k = pl.k, L = pl.order;
     int lmax = (L >= 1) ? (L - 1) / k : 0;
@@ -821,6 +835,7 @@ int moments_on_device(chebdm_handle h, const Plan& pl, int* n_gemm) {
     // split giant-step chain, which is kept in slot k + m
     auto lptr = [&](int l) -> void* {
         if (l == 1) return tslot(h, pl, k);
+        if (pl.sum) return slot(h, pl, (int64_t)k + l - 2);
         if (pl.split_h > 0 && l == pl.split_h) return slot(h, pl, (int64_t)k + pl.m);
         if (pl.split_q > 0 && l == pl.split_q) return slot(h, pl, (int64_t)k + pl.m + 1);
         return rslot(h, pl, l - 2);
@@ -864,7 +879,14 @@ int giant_steps(chebdm_handle h, const Plan& pl, double* dD, int64_t ldd, int* n
                                       (float*)rslot(h, pl, 0), pl.n, pl.ld, h->stream));
     CHECK(prof_end(h, ev));
     rns_forget(h, rslot(h, pl, 0), rslot(h, pl, m));   // the ladder's matrices made room for the blocks
-    if (m == 1) {
+    if (pl.sum) {
+        CHECK(prof_begin(h, PROF_GEMM, m - 1, (m - 1) * sym_product_flop(pl.n), 0.0, &ev));
+        HIP_TRY(launch_product_sum((const double*)tslot(h, pl, k), (const double*)rslot(h, pl, 1), stride, m - 1,
+                                   (const double*)rslot(h, pl, 0), pl.n, pl.ld, dD, ldd, h->gemm_scratch,
+                                   kGemmScratchBytes, h->stream));
+        CHECK(prof_end(h, ev));
+        *n_gemm += m - 1;
+    } else if (m == 1) {
         HIP_TRY(launch_copy_out(rslot(h, pl, 0), pl.elem == 8, pl.ld, pl.n, dD, ldd, h->stream));
     } else {
         void* Y = k >= 1 ? tslot(h, pl, k) : nullptr;
@@ -1227,7 +1249,8 @@ int chebdm_mu_search(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, 
     CHECK(plan_quadrature(pl, beta, emin, emax));
     CHECK(ensure_small(h, pl.M));
     pl.ld = round_up(n, 128);
-    pl.split_h = two_chain_split(pl, dD != nullptr);
+    pl.sum = dD && sum_pays(pl);
+    pl.split_h = two_chain_split(pl, dD != nullptr && !pl.sum);
     pl.split_q = four_chain_split(pl, pl.split_h);
     CHECK(ensure_mats(h, pl, pl.k + pl.m + extra_chain_slots(pl)));
     CHECK(ensure_rns(h, pl));
@@ -1281,7 +1304,7 @@ int chebdm_workspace_size(chebdm_handle h, int64_t n, int32_t order, const chebd
     const int64_t M = opts && opts->n_quad > 0 ? opts->n_quad : (int64_t)1 << 16;
     const bool comp = pl.form == CHEBDM_GIANT_COMPOSITION && pl.chains != 1;
     const bool four = comp && pl.m >= 8 && (pl.chains == 4 || (pl.chains == 0 && four_chains_pay(pl)));
-    const int64_t slots = pl.k + pl.m + (comp && pl.m >= 4 ? 1 : 0) + (four ? 1 : 0);
+    const int64_t slots = pl.k + pl.m + (sum_pays(pl) ? pl.m - 2 : (comp && pl.m >= 4 ? 1 : 0) + (four ? 1 : 0));
     *bytes = (size_t)slots * (size_t)ld * (size_t)ld * pl.elem + small_bytes_for(M);
     *bytes += kGemmScratchBytes;
     return CHEBDM_OK;

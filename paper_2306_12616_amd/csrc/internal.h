@@ -140,6 +140,11 @@ hipError_t launch_gemm_f32(const GemmBatch<float>& b, int64_t n, int64_t ld, int
 bool gemm_small_pays(int64_t n, int count);
 hipError_t launch_gemm_small(const GemmBatch<double>& b, int64_t n, int64_t ld, hipStream_t st);
 
+// ---- D = R0 + sum_{l < prods} T_l R_l over symmetric ld x ld matrices `stride` apart (k_sum.hip); the
+// scratch holds at least 8 parts of every 32 x 32 tile on and above the diagonal (64 MB: n <= 1408)
+hipError_t launch_product_sum(const double* T, const double* R, int64_t stride, int prods, const double* R0, int64_t n,
+                              int64_t ld, double* D, int64_t ldd, void* scratch, size_t scratch_bytes, hipStream_t st);
+
 // ---- float64 products by residue arithmetic on int8 MFMA (k_rns.hip)
 constexpr int kRnsModuli = 15;
 constexpr int kRnsGroup = 16;   // operands or products of one launch
