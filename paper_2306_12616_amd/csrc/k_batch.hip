@@ -336,37 +336,22 @@ k_batch_tau(const BatchGeom* __restrict__ geo, const double* __restrict__ trb, c
 }
 
 // ---- quadrature tables and the bisection
+// (transforms of cheb_dev.h; TERMS: the reduced forms.  128 problems of 96..1024, order 256, float32: DCT-III
+// 1103 -> 454 us and DCT-II 887 -> 664 with mirrored nodes and 32-bit angles without a division, the same
+// bits; 40 of 96..256, float64, whole call 3.07 -> 2.73 ms with turned angles)
+template <bool TERMS>
 __global__ void __launch_bounds__(256)
 k_batch_dct3(const double* __restrict__ tau, int order, const int64_t* __restrict__ mq, int64_t mcap,
              double* __restrict__ w, double* __restrict__ x, int damping) {
     extern __shared__ double st[];
     const int p = blockIdx.y;
+    const int64_t M = mq[p];
     // the grid spans the largest quadrature the plan allows; work-groups past this problem's
-    // M nodes (64 per work-group) leave at once, before staging the moments
-    if ((int64_t)blockIdx.x * 64 >= mq[p]) return;
-    for (int i = threadIdx.x; i <= order; i += 256)
-        st[i] = tau[(int64_t)p * (order + 1) + i] * damping_factor(damping, i, order);
+    // M nodes (64 pairs per work-group) leave at once, before staging the moments
+    if ((int64_t)blockIdx.x * (256 / kDctSplit) >= (M + 1) / 2) return;
+    dct3_stage<TERMS>(tau + (int64_t)p * (order + 1), order, damping, st);
     __syncthreads();
-    // four neighbouring lanes share node j, lane s summing n = s, s + 4, ... (as k_dct3)
-    const int s = threadIdx.x & 3;
-    const int64_t M = mq[p], j = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 2;
-    const bool live = j < M;   // no early exit: every lane takes part in the shuffles
-    const int64_t mod = 4 * M, q1 = 2 * j + 1, step = (4 * q1) % mod;
-    double acc = 0.0;
-    if (live) {
-        int64_t q = (s * q1) % mod;
-        for (int nn = s; nn <= order; nn += 4) {
-            acc += nn == 0 ? st[0] : 2.0 * st[nn] * node_cos(q, M);
-            q += step;
-            if (q >= mod) q -= mod;
-        }
-    }
-    acc += __shfl_xor(acc, 1, 64);
-    acc += __shfl_xor(acc, 2, 64);
-    if (live && s == 0) {
-        w[p * mcap + j] = acc;
-        x[p * mcap + j] = node_cos(q1, M);
-    }
+    dct3_pair<TERMS>(st, order, M, ((int64_t)blockIdx.x * 256 + threadIdx.x) / kDctSplit, w + p * mcap, x + p * mcap);
 }
 
 constexpr int kBisect = 512;
@@ -406,22 +391,15 @@ k_batch_fermi(const int64_t* __restrict__ mq, int64_t mcap, const DevScalars* __
     f[p * mcap + j] = fermi_scaled(node_cos(2 * j + 1, M), s[p].beta_s, s[p].mu_s);
 }
 
+template <bool TERMS>
 __global__ void __launch_bounds__(256)
 k_batch_dct2(const int64_t* __restrict__ mq, int64_t mcap, const double* __restrict__ f, int order,
              double* __restrict__ c, int damping) {
     __shared__ double smem[4];
     const int p = blockIdx.y;
-    const int64_t n = blockIdx.x, M = mq[p], mod = 4 * M;
-    const int64_t step = (512 * n) % mod;
-    int64_t q = (n * (2 * (int64_t)threadIdx.x + 1)) % mod;
+    const int64_t n = blockIdx.x, M = mq[p];
     const double* fp = f + p * mcap;
-    double acc = 0.0;
-    for (int64_t j = threadIdx.x; j < M; j += 256) {
-        acc += fp[j] * node_cos(q, M);
-        q += step;
-        if (q >= mod) q -= mod;
-    }
-    acc = block_sum<256>(acc, smem);
+    const double acc = block_sum<256>(TERMS ? dct2_terms(n, M, fp) : dct2_turned(n, M, fp), smem);
     if (threadIdx.x == 0)
         c[(int64_t)p * (order + 1) + n] = (n == 0 ? 1.0 : 2.0) * acc / (double)M * damping_factor(damping, (int)n, order);
 }
@@ -680,8 +658,9 @@ hipError_t launch_batch_moments(const BatchDims& d, const BatchGeom* geo, const 
 hipError_t launch_batch_search(const BatchDims& d, const double* tau, const int64_t* mq, double* w, double* x,
                                DevScalars* s, int mode, const float* mu_hat, double delta, double* scratch,
                                hipStream_t st) {
-    hipLaunchKernelGGL(k_batch_dct3, dim3((unsigned)((4 * d.mcap + 255) / 256), (unsigned)d.count), dim3(256),
-                       sizeof(double) * (size_t)(d.order + 1), st, tau, d.order, mq, d.mcap, w, x, d.damping);
+    hipLaunchKernelGGL(d.prec == CHEBDM_FP64 ? k_batch_dct3<false> : k_batch_dct3<true>,
+                       dim3((unsigned)(((d.mcap + 1) / 2 * kDctSplit + 255) / 256), (unsigned)d.count), dim3(256),
+                       sizeof(double) * (size_t)dct3_padded(d.order), st, tau, d.order, mq, d.mcap, w, x, d.damping);
     hipLaunchKernelGGL(k_batch_search, dim3((unsigned)d.count), dim3(kBisect), 0, st, mq, d.mcap, (const double*)w,
                        (const double*)x, s, mode, mu_hat, delta, scratch);
     return hipGetLastError();
@@ -697,7 +676,7 @@ hipError_t launch_batch_coeffs(const BatchDims& d, const int64_t* mq, const DevS
                                double* coef, hipStream_t st) {
     hipLaunchKernelGGL(k_batch_fermi, dim3((unsigned)((d.mcap + 255) / 256), (unsigned)d.count), dim3(256), 0, st, mq,
                        d.mcap, s, ftab);
-    hipLaunchKernelGGL(k_batch_dct2, dim3((unsigned)(d.order + 1), (unsigned)d.count), dim3(256), 0, st, mq, d.mcap,
+    hipLaunchKernelGGL(d.prec == CHEBDM_FP64 ? k_batch_dct2<false> : k_batch_dct2<true>, dim3((unsigned)(d.order + 1), (unsigned)d.count), dim3(256), 0, st, mq, d.mcap,
                        (const double*)ftab, d.order, c, d.damping);
     hipLaunchKernelGGL(k_batch_cform, dim3((unsigned)d.count), dim3(64), 0, st, (const double*)c, d.order, d.k, d.m,
                        coef);

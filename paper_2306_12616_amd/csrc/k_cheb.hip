@@ -51,74 +51,15 @@ k_fermi_table(int64_t M, const DevScalars* __restrict__ s, double* __restrict__ 
     f[j] = fermi_scaled(x, s->beta_s, s->mu_s);
 }
 
-// Cosines along an arithmetic sequence of angles: an exactly reduced sincospi every kTurn terms and
-// plane rotations between, within kTurn ulp of 1.  A cospi per term bound these transforms
-// (M (L + 1) of them).  c_n against long double sums, order 512, M = 16384: at most 2.2e-17 off, 3.9e-18
-// rms (with a cospi per term 1.9e-17 and 3.3e-18, with eight terms a turn 2.5e-17 and 4.8e-18 for
-// 1 us less).
-constexpr int kTurn = 4;
-
-__device__ __forceinline__ void node_sincos(int64_t q, int64_t M, double& s, double& c) {
-    sincospi((double)q / (double)(2 * M), &s, &c);
-}
-
-// One workgroup per coefficient n: c_n = (2 - delta_{n0})/M sum_j f_j cos(n theta_j).  Nodes j and
-// M-1-j are mirror images: cos(n theta_{M-1-j}) = (-1)^n cos(n theta_j).  Order 512, M = 16384:
-// 30 us with a cospi per node, 11 us now.
+// One workgroup per coefficient n: c_n = (2 - delta_{n0})/M sum_j f_j cos(n theta_j).  Order 512,
+// M = 16384: 30 us with a cospi per node, 11 us with mirrored nodes and turned angles; TERMS (the
+// reduced forms, dct2_terms) 28 -> 21 us.
+template <bool TERMS>
 __global__ void __launch_bounds__(256)
 k_dct2(int64_t M, const double* __restrict__ f, double* __restrict__ c, int order, int damping) {
     __shared__ double smem[4];
     const int64_t n = blockIdx.x;
-    const int64_t mod = 4 * M, half = M / 2;
-    // q_j = n (2j+1) mod 4M, advanced by 2n*256 per stride without a 64-bit divide
-    const int64_t step = (512 * n) % mod, turn = (kTurn * step) % mod;
-    int64_t q = (n * (2 * (int64_t)threadIdx.x + 1)) % mod;
-    double ds, dc;
-    node_sincos(step, M, ds, dc);
-    const double sign = n % 2 ? -1.0 : 1.0;
-    double acc = 0.0;
-    for (int64_t j0 = threadIdx.x; j0 < half; j0 += 256 * kTurn) {
-        double g[kTurn], cs, sn;
-#pragma unroll
-        for (int u = 0; u < kTurn; ++u) {
-            const int64_t j = j0 + 256 * u, jc = j < half ? j : half - 1;
-            const double v = fma(sign, f[M - 1 - jc], f[jc]);
-            g[u] = j < half ? v : 0.0;
-        }
-        node_sincos(q, M, sn, cs);
-#pragma unroll
-        for (int u = 0; u < kTurn; ++u) {
-            acc = fma(g[u], cs, acc);
-            const double t = fma(cs, dc, -sn * ds);
-            sn = fma(sn, dc, cs * ds);
-            cs = t;
-        }
-        q += turn;
-        if (q >= mod) q -= mod;
-    }
-    if (M % 2 && threadIdx.x == 0) acc = fma(f[half], node_cos((n * M) % mod, M), acc);   // the node x = 0
-    acc = block_sum<256>(acc, smem);
-    if (threadIdx.x == 0) c[n] = (n == 0 ? 1.0 : 2.0) * acc / (double)M * damping_factor(damping, (int)n, order);
-}
-
-// The same sums with a cospi per term, for the reduced forms: their block sums are rounded to float32,
-// where a last-digit change of c_n moves entries of D by a float32 ulp, so they keep the sums (and
-// the bits) they had.
-__global__ void __launch_bounds__(256)
-k_dct2_terms(int64_t M, const double* __restrict__ f, double* __restrict__ c, int order, int damping) {
-    __shared__ double smem[4];
-    const int64_t n = blockIdx.x;
-    const int64_t mod = 4 * M;
-    // q_j = n (2j+1) mod 4M, advanced by 2n*256 per stride without a 64-bit divide
-    const int64_t step = (512 * n) % mod;
-    int64_t q = (n * (2 * (int64_t)threadIdx.x + 1)) % mod;
-    double acc = 0.0;
-    for (int64_t j = threadIdx.x; j < M; j += 256) {
-        acc += f[j] * node_cos(q, M);
-        q += step;
-        if (q >= mod) q -= mod;
-    }
-    acc = block_sum<256>(acc, smem);
+    const double acc = block_sum<256>(TERMS ? dct2_terms(n, M, f) : dct2_turned(n, M, f), smem);
     if (threadIdx.x == 0) c[n] = (n == 0 ? 1.0 : 2.0) * acc / (double)M * damping_factor(damping, (int)n, order);
 }
 
@@ -246,85 +187,17 @@ k_assemble_moments(const double* __restrict__ tr_baby, const double* __restrict_
     for (int i = tid; i <= order; i += 256) tau[i] = t[i];
 }
 
-// w_j = sum_n (2 - delta_{n0}) tau_n cos(n theta_j) at the nodes j and M-1-j (the even n add up, the
-// odd ones change sign); also stores x_j.  kDctSplit neighbouring lanes share a pair of nodes, lane s
-// summing n = s, s + kDctSplit, ...; 64 pairs per work-group.  Order 512, M = 16384: 33 us with a
-// cospi per node and term, 13 us now.
-constexpr int kDctSplit = 4;
-
+// w_j = sum_n (2 - delta_{n0}) tau_n cos(n theta_j) at the nodes j and M-1-j; also stores x_j.  Order 512,
+// M = 16384: 33 us with a cospi per node and term, 13 us with mirrored nodes and turned angles; TERMS
+// 31 -> 28 us.
+template <bool TERMS>
 __global__ void __launch_bounds__(256)
-k_dct3(const double* __restrict__ tau, int order, int64_t M, double* __restrict__ w,
-       double* __restrict__ x_tab, int damping) {
-    static_assert(kDctSplit == 4, "two shuffle steps");
-    extern __shared__ double st[];   // (2 - delta_{n0}) tau_n, zero up to a whole turn of every lane
-    const int padded = (order / (kDctSplit * kTurn) + 1) * kDctSplit * kTurn;
-    // with damping, t(mu~) = sum_n g_n c_n(mu~) tau_n: the factors go onto the moments
-    for (int i = threadIdx.x; i < padded; i += 256)
-        st[i] = i <= order ? (i == 0 ? 1.0 : 2.0) * (tau[i] * damping_factor(damping, i, order)) : 0.0;
-    __syncthreads();
-    const int s = threadIdx.x % kDctSplit;
-    const int64_t j = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kDctSplit;
-    const bool live = j < (M + 1) / 2;   // no early exit: every lane takes part in the shuffles
-    const int64_t mod = 4 * M, q1 = 2 * j + 1, step = (kDctSplit * q1) % mod, turn = (kTurn * step) % mod;
-    double acc = 0.0;
-    if (live) {
-        double ds, dc;
-        node_sincos(step, M, ds, dc);
-        int64_t q = (s * q1) % mod;   // n q1 mod 4M for n = s
-        for (int nn = s; nn <= order; nn += kDctSplit * kTurn) {
-            double cs, sn;
-            node_sincos(q, M, sn, cs);
-#pragma unroll
-            for (int u = 0; u < kTurn; ++u) {
-                acc = fma(st[nn + kDctSplit * u], cs, acc);
-                const double t = fma(cs, dc, -sn * ds);
-                sn = fma(sn, dc, cs * ds);
-                cs = t;
-            }
-            q += turn;
-            if (q >= mod) q -= mod;
-        }
-    }
-    acc += __shfl_xor(acc, 2, 64);                   // lanes 0, 2: the even n; lanes 1, 3: the odd ones
-    const double other = __shfl_xor(acc, 1, 64);
-    if (live && s == 0) {
-        const double xj = node_cos(q1, M);
-        w[j] = acc + other;
-        x_tab[j] = xj;
-        if (M - 1 - j != j) {
-            w[M - 1 - j] = acc - other;
-            x_tab[M - 1 - j] = -xj;
-        }
-    }
-}
-
-// The same with a cospi per node and term, for the reduced forms (as k_dct2_terms).
-__global__ void __launch_bounds__(256)
-k_dct3_terms(const double* __restrict__ tau, int order, int64_t M, double* __restrict__ w,
-       double* __restrict__ x_tab, int damping) {
+k_dct3(const double* __restrict__ tau, int order, int64_t M, double* __restrict__ w, double* __restrict__ x_tab,
+       int damping) {
     extern __shared__ double st[];
-    // with damping, t(mu~) = sum_n g_n c_n(mu~) tau_n: the factors go onto the moments
-    for (int i = threadIdx.x; i <= order; i += 256) st[i] = tau[i] * damping_factor(damping, i, order);
+    dct3_stage<TERMS>(tau, order, damping, st);
     __syncthreads();
-    const int s = threadIdx.x % kDctSplit;
-    const int64_t j = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kDctSplit;
-    const bool live = j < M;   // no early exit: every lane takes part in the shuffles
-    const int64_t mod = 4 * M, q1 = 2 * j + 1, step = (kDctSplit * q1) % mod;
-    double acc = 0.0;
-    if (live) {
-        int64_t q = (s * q1) % mod;   // n q1 mod 4M for n = s
-        for (int nn = s; nn <= order; nn += kDctSplit) {
-            acc += nn == 0 ? st[0] : 2.0 * st[nn] * node_cos(q, M);
-            q += step;
-            if (q >= mod) q -= mod;
-        }
-    }
-    acc += __shfl_xor(acc, 1, 64);
-    acc += __shfl_xor(acc, 2, 64);
-    if (live && s == 0) {
-        w[j] = acc;
-        x_tab[j] = node_cos(q1, M);
-    }
+    dct3_pair<TERMS>(st, order, M, ((int64_t)blockIdx.x * 256 + threadIdx.x) / kDctSplit, w, x_tab);
 }
 
 constexpr int kBisectThreads = 1024;
@@ -497,7 +370,7 @@ hipError_t launch_fermi_coeffs(int order, int M, const DevScalars* s, double* f_
                                hipStream_t st, int damping, int terms) {
     hipLaunchKernelGGL(k_fermi_table, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st,
                        (int64_t)M, s, f_tab);
-    hipLaunchKernelGGL(terms ? k_dct2_terms : k_dct2, dim3((unsigned)(order + 1)), dim3(256), 0, st, (int64_t)M,
+    hipLaunchKernelGGL(terms ? k_dct2<true> : k_dct2<false>, dim3((unsigned)(order + 1)), dim3(256), 0, st, (int64_t)M,
                        (const double*)f_tab, c_out, order, damping);
     return hipGetLastError();
 }
@@ -519,10 +392,9 @@ hipError_t launch_assemble_moments(const double* tr_baby, const double* gram, in
 
 hipError_t launch_dct3(const double* tau, int order, int M, double* w, double* x_tab,
                        hipStream_t st, int damping, int terms) {
-    const size_t shmem = sizeof(double) * (size_t)(order / (kDctSplit * kTurn) + 1) * kDctSplit * kTurn;   // >= order + 1
-    const int64_t threads = (terms ? (int64_t)M : ((int64_t)M + 1) / 2) * kDctSplit;
-    hipLaunchKernelGGL(terms ? k_dct3_terms : k_dct3, dim3((unsigned)((threads + 255) / 256)), dim3(256), shmem, st,
-                       tau, order, (int64_t)M, w, x_tab, damping);
+    const int64_t threads = ((int64_t)M + 1) / 2 * kDctSplit;
+    hipLaunchKernelGGL(terms ? k_dct3<true> : k_dct3<false>, dim3((unsigned)((threads + 255) / 256)), dim3(256),
+                       sizeof(double) * (size_t)dct3_padded(order), st, tau, order, (int64_t)M, w, x_tab, damping);
     return hipGetLastError();
 }
 
