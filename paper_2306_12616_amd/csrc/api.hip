@@ -870,13 +870,24 @@ int giant_steps(chebdm_handle h, const Plan& pl, double* dD, int64_t ldd, int* n
     const int k = pl.k, m = pl.m;
     const int64_t stride = pl.ld * pl.ld;
     size_t ev;
-    CHECK(prof_begin(h, PROF_COMBINE, 0, 0.0, (double)(k - 1 + m) * pl.n * pl.n * pl.elem, &ev));
+    // blocks that are operands of a product: each chain's last one (all of them in the sum of products)
+    const int hs = pl.split_h, qs = pl.split_q;
+    int heads[4] = {m - 1}, nheads = 1;
+    if (pl.form == CHEBDM_GIANT_COMPOSITION && hs > 0) heads[nheads++] = hs - 1;
+    if (pl.form == CHEBDM_GIANT_COMPOSITION && qs > 0) {
+        heads[nheads++] = qs - 1;
+        heads[nheads++] = hs + qs - 1;
+    }
+    const int* operands = pl.sum ? nullptr : heads;
+    const bool upper = operands && pl.n >= combine_upper_min_n(pl.elem);
+    CHECK(prof_begin(h, PROF_COMBINE, 0, 0.0,
+                     (double)(k - 1 + m) * pl.n * (upper ? 0.5 * (pl.n + 32) : (double)pl.n) * pl.elem, &ev));
     if (pl.elem == 8)
         HIP_TRY(launch_combine<double>((const double*)tslot(h, pl, 1), stride, k, m, h->coef,
-                                       (double*)rslot(h, pl, 0), pl.n, pl.ld, h->stream));
+                                       (double*)rslot(h, pl, 0), pl.n, pl.ld, h->stream, operands, nheads));
     else
         HIP_TRY(launch_combine<float>((const float*)tslot(h, pl, 1), stride, k, m, h->coef,
-                                      (float*)rslot(h, pl, 0), pl.n, pl.ld, h->stream));
+                                      (float*)rslot(h, pl, 0), pl.n, pl.ld, h->stream, operands, nheads));
     CHECK(prof_end(h, ev));
     rns_forget(h, rslot(h, pl, 0), rslot(h, pl, m));   // the ladder's matrices made room for the blocks
     if (pl.sum) {

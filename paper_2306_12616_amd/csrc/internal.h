@@ -115,10 +115,15 @@ hipError_t launch_bisect(const double* w, const double* x_tab, int M, DevScalars
                          double* work, hipStream_t st);
 
 // ---- block sums and Gram contractions (k_combine.hip)
-// R_l = sum_{i<k} coef[l*k + i] T_i for l < m (T_0 = I implicit, T_i = tbase + (i-1)*stride)
+// Smaller blocks are formed whole.  Float64 calls of those sizes mirror one block (fixed mu; N = 700 791 ->
+// 768 us, 600 no change), the reduced forms' four (float32 N = 1000 1256 -> 1263 us, 2000 5491 -> 5412).
+constexpr int64_t combine_upper_min_n(size_t elem) { return elem == 8 ? 700 : 1200; }
+// R_l = sum_{i<k} coef[l*k + i] T_i for l < m (T_0 = I implicit, T_i = tbase + (i-1)*stride);
+// operands (count <= 4): the blocks needed whole, the others may come on and above the diagonal only
 template <typename T>
 hipError_t launch_combine(const T* tbase, int64_t stride, int k, int m, const double* coef,
-                          T* rbase, int64_t n, int64_t ld, hipStream_t st);
+                          T* rbase, int64_t n, int64_t ld, hipStream_t st, const int* operands = nullptr,
+                          int count = 0);
 // G[l][i] = <L_l, T_i> (Frobenius) for l < nl, i < nt; L_l, T_i given by pointer lists,
 // n rows of ld with a zero padding; float64 matrices are symmetric (their upper triangles are read)
 template <typename T>

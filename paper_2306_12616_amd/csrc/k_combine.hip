@@ -10,6 +10,14 @@
 // Full padded rows are processed: the zero padding of T_i yields zero
 // padding in R_l, so no column predicate is needed.
 //
+// Upper form: all matrices are exactly symmetric and the giant steps read a block as an addend on and
+// above the diagonal only, so each row starts at its diagonal block of kUpper columns; the few
+// blocks that are operands (a chain's first) are mirrored into their lower parts by a second launch.
+// Order 512 (22 + 23 matrices, mirrors included), full -> upper, us: float64
+// N = 2000 301 -> 205, 3001 669 -> 393, 4000 1137 -> 679 (order 2048, 45 + 46 matrices, 5000 5875 -> 3275), float32
+// N = 2000 203 -> 139.  A row is followed by its mirror row n - 1 - y: single short rows of a power-of-two ld
+// fall on few memory channels (N = 4000 1025 us without the mirrors).
+//
 // Gram: G[l][i] = <L_l, T_i>_F (= tr(L_l T_i) for symmetric matrices), the
 // (nl x N^2)(N^2 x nt) contraction behind the trace moments.  It runs on the
 // float64 MFMA units with the matrices' elements as the K dimension; float
@@ -34,8 +42,9 @@ template <> struct Vec<double> { using V = f64x2; static constexpr int W = 2; };
 template <> struct Vec<float> { using V = f32x2; static constexpr int W = 2; };
 
 constexpr int kCombineThreads = 256;
+constexpr int kUpper = 32;   // the gemm tiles' epilogues read no addend left of the diagonal's block of 16
 
-template <typename T, int MB>
+template <typename T, int MB, bool UPPER>
 __global__ void __launch_bounds__(kCombineThreads)
 k_combine(const T* __restrict__ tbase, int64_t stride, int k, int l0, int lcount,
           const double* __restrict__ coef, T* __restrict__ rbase, int64_t n, int64_t ld) {
@@ -47,8 +56,15 @@ k_combine(const T* __restrict__ tbase, int64_t stride, int k, int l0, int lcount
     // 3.5 -> 4.4 / 3.6 / 4.0 TB/s).  float64 keeps the scalar loads, which measured as fast at
     // n = 4000 and 8 % faster at n = 2000.
     constexpr bool kStage = sizeof(T) == 4;
-    const int64_t row = blockIdx.y;
-    const int64_t col = ((int64_t)blockIdx.x * kCombineThreads + threadIdx.x) * W;
+    int64_t row = blockIdx.y, col = ((int64_t)blockIdx.x * kCombineThreads + threadIdx.x) * W;
+    if constexpr (UPPER) {   // rows y and n - 1 - y, one after the other: about a full row of work for every y
+        col += row / kUpper * kUpper;
+        if (col >= ld) {
+            const int64_t other = n - 1 - row;
+            col = other > row ? col - ld + other / kUpper * kUpper : ld;
+            row = other;
+        }
+    }
     const bool live = col < ld;
     const int64_t off = row * ld + (live ? col : 0);
     auto tload = [&](int j) { return *reinterpret_cast<const V*>(tbase + (int64_t)j * stride + off); };
@@ -105,6 +121,28 @@ template <typename T>
 struct PtrList {
     const T* p[kMaxBlocks];
 };
+
+// The lower part of blocks l[blockIdx.z] from the upper one: the 32 x 32 tiles above the diagonal's,
+// transposed in LDS.  (The upper form stores the diagonal's tiles whole.)
+struct MirrorList {
+    int l[4];
+};
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_mirror(T* __restrict__ rbase, int64_t stride, MirrorList list, int64_t n, int64_t ld) {
+    __shared__ T tile[kUpper][kUpper + 1];
+    // along the tile diagonals: neighbours differ in rows and columns, so in memory channels too
+    const int64_t i0 = (int64_t)blockIdx.x * kUpper, j0 = i0 + ((int64_t)blockIdx.y + 1) * kUpper;
+    if (j0 >= n) return;
+    T* R = rbase + list.l[blockIdx.z] * stride;
+    const int c = threadIdx.x % kUpper, r0 = threadIdx.x / kUpper;
+#pragma unroll
+    for (int r = r0; r < kUpper; r += 256 / kUpper) tile[r][c] = R[(i0 + r) * ld + j0 + c];
+    __syncthreads();
+#pragma unroll
+    for (int r = r0; r < kUpper; r += 256 / kUpper)
+        if (j0 + r < n && i0 + c < n) R[(j0 + r) * ld + i0 + c] = tile[c][r];
+}
 
 constexpr int kGramThreads = 256;
 constexpr int kGramMax = 48;   // rows / columns of G handled (3 MFMA blocks of 16)
@@ -289,22 +327,37 @@ void launch_gram_fm(int fn, const PtrList<T>& L, int nl, const PtrList<T>& Tm, i
 
 template <typename T>
 hipError_t launch_combine(const T* tbase, int64_t stride, int k, int m, const double* coef, T* rbase,
-                          int64_t n, int64_t ld, hipStream_t st) {
+                          int64_t n, int64_t ld, hipStream_t st, const int* operands, int count) {
     constexpr int W = Vec<T>::W;
-    if (ld % (W * 2) != 0 || k < 1 || k > kMaxBlocks) return hipErrorInvalidValue;
+    if (ld % kUpper != 0 || k < 1 || k > kMaxBlocks || count > 4) return hipErrorInvalidValue;
+    const bool upper = operands && n >= combine_upper_min_n(sizeof(T));
     const int64_t per_block = (int64_t)kCombineThreads * W;
-    dim3 grid((unsigned)((ld + per_block - 1) / per_block), (unsigned)n);
+    // upper: a pair of rows is at most 2 ld - (n - 1) + 2 (kUpper - 1) long
+    const int64_t length = upper ? 2 * ld - n + 2 * kUpper : ld;
+    dim3 grid((unsigned)((length + per_block - 1) / per_block), (unsigned)(upper ? (n + 1) / 2 : n));
     for (int l0 = 0; l0 < m; l0 += 24) {
         const int cnt = (m - l0) < 24 ? (m - l0) : 24;
-        if (cnt <= 8)
-            hipLaunchKernelGGL((k_combine<T, 8>), grid, dim3(kCombineThreads), 0, st, tbase, stride, k, l0,
-                               cnt, coef, rbase, n, ld);
-        else if (cnt <= 16)
-            hipLaunchKernelGGL((k_combine<T, 16>), grid, dim3(kCombineThreads), 0, st, tbase, stride, k, l0,
-                               cnt, coef, rbase, n, ld);
-        else
-            hipLaunchKernelGGL((k_combine<T, 24>), grid, dim3(kCombineThreads), 0, st, tbase, stride, k, l0,
-                               cnt, coef, rbase, n, ld);
+#define COMBINE(MB)                                                                                                 \
+    if (upper)                                                                                                      \
+        hipLaunchKernelGGL((k_combine<T, MB, true>), grid, dim3(kCombineThreads), 0, st, tbase, stride, k, l0, cnt, coef, \
+                           rbase, n, ld);                                                                           \
+    else                                                                                                            \
+        hipLaunchKernelGGL((k_combine<T, MB, false>), grid, dim3(kCombineThreads), 0, st, tbase, stride, k, l0, cnt, \
+                           coef, rbase, n, ld)
+        if (cnt <= 8) {
+            COMBINE(8);
+        } else if (cnt <= 16) {
+            COMBINE(16);
+        } else {
+            COMBINE(24);
+        }
+#undef COMBINE
+    }
+    if (upper) {
+        MirrorList list{};
+        for (int i = 0; i < count; ++i) list.l[i] = operands[i];
+        const unsigned nt = (unsigned)((n + kUpper - 1) / kUpper);
+        if (nt > 1) hipLaunchKernelGGL(k_mirror<T>, dim3(nt - 1, nt - 1, (unsigned)count), dim3(256), 0, st, rbase, stride, list, n, ld);
     }
     return hipGetLastError();
 }
@@ -334,9 +387,9 @@ hipError_t launch_gram(const T* const* lmats, int nl, const T* const* tmats, int
 }
 
 template hipError_t launch_combine<double>(const double*, int64_t, int, int, const double*, double*, int64_t,
-                                           int64_t, hipStream_t);
+                                           int64_t, hipStream_t, const int*, int);
 template hipError_t launch_combine<float>(const float*, int64_t, int, int, const double*, float*, int64_t,
-                                          int64_t, hipStream_t);
+                                          int64_t, hipStream_t, const int*, int);
 template hipError_t launch_gram<double>(const double* const*, int, const double* const*, int, int64_t, int64_t,
                                         double*, int64_t, double*, hipStream_t);
 template hipError_t launch_gram<float>(const float* const*, int, const float* const*, int, int64_t, int64_t,
