@@ -240,7 +240,7 @@ int enqueue(chebdm_batch_ctx* b, hipStream_t st, bool prof, bool with_density) {
     HIP_TRY(launch_batch_coeffs(d, b->mq, b->scal, b->ftab, b->c, b->coef, st));
     if (prof) {
         double bytes = 0.0;
-        for (int p = 0; p < d.count; ++p) bytes += (double)(d.k - 1 + d.m) * b->n[p] * b->n[p] * b->elem;
+        for (int p = 0; p < d.count; ++p) bytes += (double)(d.k - 1 + d.m) * b->n[p] * 0.5 * (b->n[p] + 32) * b->elem;
         CHECK(prof_begin(b->h, PROF_COMBINE, 0, 0.0, bytes, &ev));
     }
     HIP_TRY(launch_batch_combine(d, b->geo, b->coef, b->mats, st));

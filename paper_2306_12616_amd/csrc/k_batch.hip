@@ -427,8 +427,13 @@ k_batch_cform(const double* __restrict__ c, int order, int k, int m, double* __r
     for (int idx = tid; idx < k * m; idx += 64) coef[(int64_t)p * k * m + idx] = e[idx / k][idx % k];
 }
 
-// ---- block sums R_l = sum_i e_{l,i} T_i (T_0 = I), all l of a problem in one pass,
-// 16-byte vectors along full padded rows (zero padding in, zero padding out)
+// ---- block sums R_l = sum_i e_{l,i} T_i (T_0 = I), all l of a problem in one pass, 16-byte vectors
+// on and above the diagonal's blocks of kUpper columns (padding included: zero in, zero out), rows in pairs
+// (y, n - 1 - y) as in k_combine.hip.  Threads take vectors of a problem in one sequence: rows of a
+// small problem do not fill a work-group.  The last block, the chain's first operand, is mirrored by
+// k_batch_mirror.  Whole calls, float32, 128 problems of 96..1024, order 256: 25.6 -> 24.9 ms, 64 of 96..512
+// 4.13 -> 3.99, 8 of 96..256, order 64 845 -> 848 us; float64, 32 of 96..1024, order 128: 7.82 -> 7.64 ms.
+constexpr int kUpper = 32;
 template <typename T> struct BVec;
 template <> struct BVec<double> { typedef double V __attribute__((ext_vector_type(2))); static constexpr int W = 2; };
 template <> struct BVec<float> { typedef float V __attribute__((ext_vector_type(4))); static constexpr int W = 4; };
@@ -439,15 +444,22 @@ k_batch_combine(const BatchGeom* __restrict__ geo, const double* __restrict__ co
                 T* __restrict__ mats) {
     using V = typename BVec<T>::V;
     constexpr int W = BVec<T>::W;
-    const int p = blockIdx.z;
+    const int p = blockIdx.y;
     const int64_t n = geo[p].n, ld = geo[p].ld, stride = ld * ld;
-    const int64_t col = ((int64_t)blockIdx.x * 256 + threadIdx.x) * W;
-    if (col >= ld) return;
     const T* tb = mats + geo[p].off;
     T* rb = mats + geo[p].off + (int64_t)k * stride;
     const double* cf = coef + (int64_t)p * k * m;
     const int lcount = (m - l0) < MB ? (m - l0) : MB;
-    for (int64_t row = blockIdx.y; row < n; row += gridDim.y) {   // rows row, row + gridDim.y, ...
+    const uint32_t length = (uint32_t)(2 * ld - n + 2 * kUpper) / W;   // vectors of a pair of rows, at most
+    const uint32_t total = length * (uint32_t)((n + 1) / 2);
+    for (uint32_t v = blockIdx.x * 256 + threadIdx.x; v < total; v += gridDim.x * 256) {
+        int64_t row = v / length, col = (int64_t)(v % length) * W + row / kUpper * kUpper;
+        if (col >= ld) {
+            const int64_t other = n - 1 - row;
+            col = other > row ? col - ld + other / kUpper * kUpper : ld;
+            row = other;
+        }
+        if (col >= ld) continue;
         const int64_t off = row * ld + col;
         double acc[MB][W];
 #pragma unroll
@@ -474,6 +486,29 @@ k_batch_combine(const BatchGeom* __restrict__ geo, const double* __restrict__ co
                 *reinterpret_cast<V*>(rb + (int64_t)(l0 + l) * stride + off) = o;
             }
         }
+    }
+}
+
+// The lower part of block m - 1 from its upper one, 32 x 32 tiles along the diagonals.
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_batch_mirror(const BatchGeom* __restrict__ geo, int k, int m, T* __restrict__ mats) {
+    __shared__ T tile[kUpper][kUpper + 1];
+    const int p = blockIdx.y;
+    const int64_t n = geo[p].n, ld = geo[p].ld;
+    T* R = mats + geo[p].off + (int64_t)(k + m - 1) * ld * ld;
+    const int nt = (int)((n + kUpper - 1) / kUpper);
+    const int c = threadIdx.x % kUpper, r0 = threadIdx.x / kUpper;
+    for (int t = blockIdx.x; t < nt * (nt - 1); t += gridDim.x) {
+        const int64_t i0 = (int64_t)(t % nt) * kUpper, j0 = i0 + (int64_t)(t / nt + 1) * kUpper;
+        if (j0 >= n) continue;   // the whole work-group
+#pragma unroll
+        for (int r = r0; r < kUpper; r += 256 / kUpper) tile[r][c] = R[(i0 + r) * ld + j0 + c];
+        __syncthreads();
+#pragma unroll
+        for (int r = r0; r < kUpper; r += 256 / kUpper)
+            if (j0 + r < n) R[(j0 + r) * ld + i0 + c] = tile[c][r];   // i0 + 31 < j0 < n
+        __syncthreads();
     }
 }
 
@@ -526,8 +561,11 @@ inline int batch_row_groups(int64_t nmax) { return nmax < 64 ? (int)nmax : 64; }
 
 template <typename T>
 hipError_t combine_all(const BatchDims& d, const BatchGeom* geo, const double* coef, T* mats, hipStream_t st) {
-    const int64_t per = 256 * BVec<T>::W;
-    dim3 grid((unsigned)((d.ldmax + per - 1) / per), (unsigned)batch_row_groups(d.nmax), (unsigned)d.count);
+    // work-groups that share a problem's vectors: 64, more where few problems leave the chip idle
+    const int64_t vectors = (2 * d.ldmax - d.nmax + 2 * kUpper) / BVec<T>::W * ((d.nmax + 1) / 2);
+    int64_t groups = d.count < 128 ? 8192 / d.count : 64;
+    if (groups > (vectors + 255) / 256) groups = (vectors + 255) / 256;
+    dim3 grid((unsigned)groups, (unsigned)d.count);
     for (int l0 = 0; l0 < d.m; l0 += 24) {
         const int cnt = (d.m - l0) < 24 ? (d.m - l0) : 24;
         if (cnt <= 8)
@@ -537,6 +575,7 @@ hipError_t combine_all(const BatchDims& d, const BatchGeom* geo, const double* c
         else
             hipLaunchKernelGGL((k_batch_combine<T, 24>), grid, dim3(256), 0, st, geo, coef, d.k, d.m, l0, mats);
     }
+    hipLaunchKernelGGL(k_batch_mirror<T>, dim3(32, (unsigned)d.count), dim3(256), 0, st, geo, d.k, d.m, mats);
     return hipGetLastError();
 }
 

@@ -49,3 +49,28 @@ def test_stale_lower_parts(cd, prec, n, giant):
     for a, b in zip(out[:half], out[half:]):
         assert np.isfinite(a).all() and np.array_equal(a, a.T)
         assert np.array_equal(a, b)
+
+
+# rows and tiles of 32, problems smaller than a work-group's share, two blocks (order 8) and many;
+# a spoiled plan's next call against a fresh plan's
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
+@pytest.mark.parametrize("order", [8, 70, 700])
+def test_batch_stale_lower_parts(cd, prec, order):
+    sizes = [33, 64, 100, 257, 640, 1000]
+    print(f"batched block sums {prec} order={order}", flush=True)
+    Hs = [torch.from_numpy(synth.hamiltonian(n, "uniform", seed=n)[0]).cuda() for n in sizes]
+    betas, n_elecs = [BETA] * len(sizes), [n // 2 + 0.5 for n in sizes]
+    out = []
+    for spoil in (False, True):
+        handle = cd.Handle(0)
+        plan = cd.chebdm_batch_create(handle, sizes, order, cd.make_opts(prec=prec))
+        if spoil:
+            plan.mu_search([torch.full_like(h, float("nan")) for h in Hs], betas, n_elecs, allow_errors=True)
+        for _ in range(2):
+            Ds = plan.mu_search(Hs, betas, n_elecs)[1]
+            out.append([d.cpu().numpy() for d in Ds])
+        plan.close()
+        handle.close()
+    for a in out:
+        for d, e in zip(a, out[0]):
+            assert np.isfinite(d).all() and np.array_equal(d, d.T) and np.array_equal(d, e)
