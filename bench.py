@@ -27,6 +27,7 @@ if ROOT not in sys.path:
 METRIC = "density matrices/s and % MFMA peak at N=1000/4000 vs plain FP64 path"
 PEAK_TFLOPS = {"fp64": 78.6, "fp32": 157.3, "bf16x3": 2500.0, "bf16x6": 2500.0}   # dense MFMA peaks of MI355X
 PEAK_HBM_GBS = 8000.0
+INT8_MODULI, INT8_MIN_N, PEAK_INT8_TOPS = 15, 1400, 5000.0   # float64 products on the int8 units (csrc/k_rns.hip)
 SEEDS = {1000: 2000, 2000: 2001, 4000: 2002}   # gaussmix6 workloads at order 512
 ALL_SECTIONS = ("breakdown", "fixed", "config", "lanczos", "accuracy", "diag", "batch", "learned")
 
@@ -125,7 +126,7 @@ def mu_search_row(cd, handle, inputs, key, beta, order, prec, search="bisection"
     H = inputs.get(*key)
     dt, prof, info, mu, D = run_steps(cd, handle, H, beta, n / 2.0, order, cd.make_opts(prec, search=search),
                                       steps, warmup, with_out=True)
-    r = roofline_of(prof, prec)
+    r = roofline_of(prof, prec, n)
     row = {"dm_per_s": round(steps / dt, 3), "ms_per_step": round(1e3 * dt / steps, 3),
            "gemm_frac_of_peak": r["frac"] if r else None, "gemm_tflops": r["achieved"] if r else None,
            "search_ms": round(prof["search_ms"] / steps, 3), "search_evals": info["iters"],
@@ -156,6 +157,11 @@ def gemm_sources_sha256():
     return h.hexdigest()
 
 
+def on_int8(prec, n):
+    """Whether all products of a float64 call run on the int8 units (csrc/api.hip: from n = 1400)."""
+    return prec == "fp64" and n is not None and n >= INT8_MIN_N
+
+
 def traffic_of(prec, n, order):
     """HBM bytes per product-kernel launch from the committed counter summary, if it still applies.
 
@@ -165,6 +171,8 @@ def traffic_of(prec, n, order):
     the recorded value (otherwise the counters describe another kernel and traffic is null).
     """
     path = os.path.join(ROOT, "profiles", f"traffic_k_gemm_{prec}_n{n}_order{order}.txt")
+    if on_int8(prec, n):   # the record is of k_gemm, which does not run there
+        return None
     if not os.path.exists(path):
         return None
     with open(path) as f:
@@ -185,16 +193,25 @@ def run_density_steps(cd, handle, H, beta, mu, order, opts, steps, warmup):
     return dt, prof
 
 
-def roofline_of(prof, prec):
-    """Matrix-product kernel: algorithmic flops / summed launch time vs the MFMA peak."""
+def roofline_of(prof, prec, n=None):
+    """Matrix-product kernels: algorithmic flops / summed launch time vs the MFMA peak.
+
+    Float64 products on the int8 units count as their INT8_MODULI int8 products against the int8
+    peak (scale, split and join launches are in the time); ``f64_equivalent`` is the rate in
+    float64 flops.
+    """
     if prof["gemm_ms"] <= 0:
         return None
-    flop = prof["gemm_flop"] * {"bf16x3": 3.0, "bf16x6": 6.0}.get(prec, 1.0)   # bf16 products per split product
+    int8 = on_int8(prec, n)
+    # bf16 products per split product, int8 products per float64 product
+    flop = prof["gemm_flop"] * (INT8_MODULI if int8 else {"bf16x3": 3.0, "bf16x6": 6.0}.get(prec, 1.0))
     achieved = flop / (prof["gemm_ms"] * 1e-3) / 1e12
-    peak = PEAK_TFLOPS[prec]
-    return {"bound": "mfma", "achieved": round(achieved, 3), "peak": peak, "unit": "TFLOP/s",
-            "frac": round(achieved / peak, 4), "traffic": None,
-            "kernel": "k_gemm (symmetric product, fused epilogue)",
+    peak = PEAK_INT8_TOPS if int8 else PEAK_TFLOPS[prec]
+    extra = {"f64_equivalent": round(achieved / INT8_MODULI, 3)} if int8 else {}
+    return {"bound": "mfma", "achieved": round(achieved, 3), "peak": peak, "unit": "TOP/s" if int8 else "TFLOP/s",
+            "frac": round(achieved / peak, 4), "traffic": None, **extra,
+            "kernel": "k_rns_gemm (int8 products by residue arithmetic, with scale, split and join)" if int8
+                      else "k_gemm (symmetric product, fused epilogue)",
             "launches": prof["gemm_launches"], "products": prof["gemm_products"],
             "avg_launch_ms": round(prof["gemm_ms"] / max(1, prof["gemm_launches"]), 4)}
 
@@ -576,7 +593,7 @@ def main():
                                                 with_out=True)
     value = args.steps / dt
     log(f"  {value:.3f} DM/s, {1e3 * dt / args.steps:.2f} ms/step, gemm {prof['gemm_ms'] / args.steps:.2f} ms/step")
-    roof = roofline_of(prof, args.prec)
+    roof = roofline_of(prof, args.prec, n)
     if roof is not None:
         roof["traffic"] = traffic_of(args.prec, n, order)
     head_check = {}
@@ -639,7 +656,7 @@ def main():
             D = torch.empty_like(hh)
             d3, p3, (_, i3) = timed(lambda: cd.chebdm_density(handle, hh, beta, mu_nn, order, cd.make_opts(pr), D=D),
                                     steps, 2, cd, handle)
-            r3 = roofline_of(p3, pr)
+            r3 = roofline_of(p3, pr, nn)
             fixed[f"n{nn}_{pr}"] = row = {"dm_per_s": round(steps / d3, 3), "ms_per_step": round(1e3 * d3 / steps, 3),
                                           "products": p3["gemm_products"] // steps,
                                           "gemm_frac_of_peak": r3["frac"] if r3 else None}
