@@ -317,10 +317,10 @@ int chebdm_mu_search(chebdm_handle h, const double* dH, int64_t n, int64_t ldh,
  * has needed): the matrix workspace, (k + m) ld^2 elements (k + m + 1 for
  * the composition form with m >= 4: the two-chain giant steps keep T_h(T_k);
  * k + m + 2 where the giant steps go in four chains: they also keep T_q(T_k);
- * k + 2 m - 2 for float64 up to n = 1152, whose mu search keeps its ladder)
+ * k + 2 m - 2 for float64 up to n = 1344, whose mu search keeps its ladder)
  * with ld = round_up(n, 128) and 8 (float64) or 4 bytes per element, plus the
  * small buffers sized for opts->n_quad quadrature nodes (2^16 when 0), plus
- * 64 MB of product scratch (partial sums of K-sliced product tiles).
+ * 96 MB of product scratch (partial sums of K-sliced product tiles).
  * Float64 calls from n = 960 on also hold residue planes of their operands
  * (at most 8.5 GB) where there is memory for them; they are not in the size.
  * Needs no device; h may be NULL.  ERR_ARG on bad sizes or options.

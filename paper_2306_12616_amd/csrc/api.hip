@@ -461,8 +461,9 @@ int four_chain_split(const Plan& pl, int split_h) {
 
 // Whether the density is one sum of products with the ladder's matrices: float64 composition form
 // where the library chooses, with a ladder up to T_{(m-1)k} (an order that k divides ends one short).
-// Up to N = 1152: past it the chains' products on the int8 units are as fast (k_sum.hip has both sides).
-constexpr int64_t kSumMaxN = 1152;
+// Up to N = 1344, where the scratch ends: from there on the chains' products run on the int8 units at about
+// the same speed (k_sum.hip has both sides).
+constexpr int64_t kSumMaxN = 1344;
 bool sum_pays(const Plan& pl) {
     return pl.prec == CHEBDM_FP64 && pl.form == CHEBDM_GIANT_COMPOSITION && pl.chains == 0 && pl.m >= 3 &&
            (pl.order - 1) / pl.k >= pl.m - 1 && pl.n <= kSumMaxN;

@@ -134,7 +134,7 @@ hipError_t launch_gram(const T* const* lmats, int nl, const T* const* tmats, int
 // scratch (nullable; kGemmScratchBytes is enough): partial accumulators of the K-sliced tiles
 // of a launch's last, nearly empty round, or the pieces of stream-K launches (without scratch the launch
 // runs unsplit)
-constexpr size_t kGemmScratchBytes = (size_t)64 << 20;
+constexpr size_t kGemmScratchBytes = (size_t)96 << 20;
 hipError_t launch_gemm_f64(const GemmBatch<double>& b, int64_t n, int64_t ld, hipStream_t st,
                            void* scratch = nullptr, size_t scratch_bytes = 0);
 // split: 0 float32 MFMA, 1 bf16x3, 2 bf16x6
@@ -145,8 +145,8 @@ hipError_t launch_gemm_f32(const GemmBatch<float>& b, int64_t n, int64_t ld, int
 bool gemm_small_pays(int64_t n, int count);
 hipError_t launch_gemm_small(const GemmBatch<double>& b, int64_t n, int64_t ld, hipStream_t st);
 
-// ---- D = R0 + sum_{l < prods} T_l R_l over symmetric ld x ld matrices `stride` apart (k_sum.hip); the
-// scratch holds at least 8 parts of every 32 x 32 tile on and above the diagonal (64 MB: n <= 1408)
+// ---- D = R0 + sum_{l < prods} T_l R_l over symmetric ld x ld matrices `stride` apart (k_sum.hip);
+// kGemmScratchBytes of scratch are enough up to n = 1344
 hipError_t launch_product_sum(const double* T, const double* R, int64_t stride, int prods, const double* R0, int64_t n,
                               int64_t ld, double* D, int64_t ldd, void* scratch, size_t scratch_bytes, hipStream_t st);
 

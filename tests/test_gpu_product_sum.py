@@ -23,11 +23,12 @@ def cd():
     return m
 
 
-# 32-tiles to 560, 48-tiles, 64-tiles where the padding ends before the last 48-tile (625..640, 865..896,
-# 1009..1024), chains from 1153; order 8 has three blocks, order 72 = 9 * 8 no T_72 in its ladder
+# 32-tiles to 560, 48-tiles to 700 (32-tiles where the padding ends before the last one, 625..640), ranges of
+# 96-tiles, chains from 1345; order 8 has three blocks, order 72 = 9 * 8 no T_72 in its ladder
 @pytest.mark.parametrize("n,order", [(16, 80), (17, 8), (32, 80), (33, 80), (64, 8), (129, 80), (559, 80), (560, 80),
-                                     (561, 80), (624, 80), (625, 80), (768, 80), (865, 80), (1008, 80), (1009, 80),
-                                     (1151, 80), (1152, 80), (1153, 80), (300, 72), (300, 73)])
+                                     (561, 80), (624, 80), (625, 80), (700, 80), (701, 80), (701, 8), (768, 80), (769, 80),
+                                     (865, 80), (1008, 80), (1009, 80), (1152, 80), (1153, 80), (1344, 80),
+                                     (1344, 8), (1345, 80), (300, 72), (300, 73)])
 def test_mu_search_and_density(cd, n, order):
     print(f"product sum n={n} order={order}", flush=True)
     h, q, lam = synth.hamiltonian(n, "uniform", seed=n)
