@@ -25,15 +25,16 @@
 // independent loads go out together at the top of a kernel, loops run in whole chunks of
 // unconditional loads (remainder iterations are waited for one by one), and the
 // reorthogonalisation has a thread per element instead of one per four: 40 steps at
-// N = 2000 took 1050 us and take 790 now.  The sums keep their order, bit for bit: the reduced
+// N = 2000 took 1050 us and take 730 now (n = 128, 80 steps: 1040 and 1020).  The sums keep their order, bit for bit: the reduced
 // forms round T_1 and its descendants to float32, where a last-digit change of the bounds moves
 // entries of D by a float32 ulp.  (A two-launch step, with the projections taken from partials of
-// v_i . w and (H v_i) . w, measured 692 us and was given up for that.)
+// v_i . w and (H v_i) . w, measured 692 us when this form took 790, and was given up for that.)
 //
 // The same kernels serve one problem and a batch of problems of different n
 // (the batched form): blockIdx.y (blockIdx.z for the projections) selects the
 // problem, whose workspace, scalars and step count min(steps, n) are its own.
 #include <cmath>
+#include <type_traits>
 
 #include "internal.h"
 #include "reduce.h"
@@ -158,24 +159,30 @@ __global__ void __launch_bounds__(kNT) k_lz_matvec(const LanczosRun r, int j) {
     const double* h1 = q.H + (int64_t)(r0 + 1 < n ? r0 + 1 : n - 1) * q.ldh;
     const NormLoads pn = norm_loads(q.L.pn, q.nbv);
     double y[kRowsPerWave] = {0.0, 0.0};
-    constexpr int U = 16;
+    auto rows = [&](auto chunk) {
+        constexpr int U = decltype(chunk)::value;
 #pragma unroll 1
-    for (int c0 = lane; c0 < n; c0 += 64 * U) {
-        double x[U], a[U], b[U];
+        for (int c0 = lane; c0 < n; c0 += 64 * U) {
+            double x[U], a[U], b[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int c = c0 + 64 * u, cc = c < n ? c : n - 1;
-            x[u] = w[cc];
-            a[u] = h0[cc];
-            b[u] = h1[cc];
-        }
+            for (int u = 0; u < U; ++u) {
+                const int c = c0 + 64 * u, cc = c < n ? c : n - 1;
+                x[u] = w[cc];
+                a[u] = h0[cc];
+                b[u] = h1[cc];
+            }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const double xu = c0 + 64 * u < n ? x[u] : 0.0;
-            y[0] = fma(a[u], xu, y[0]);
-            y[1] = fma(b[u], xu, y[1]);
+            for (int u = 0; u < U; ++u) {
+                const double xu = c0 + 64 * u < n ? x[u] : 0.0;
+                y[0] = fma(a[u], xu, y[0]);
+                y[1] = fma(b[u], xu, y[1]);
+            }
         }
-    }
+    };
+    // longer chunks would be mostly repeats of the last element: 4.8 -> 3.7 us a step at n = 128
+    if (n <= 256) rows(std::integral_constant<int, 4>{});
+    else if (n <= 512) rows(std::integral_constant<int, 8>{});
+    else rows(std::integral_constant<int, 16>{});
     if (broken) return;
     const double bt = sqrt(norm_total(pn, q.nbv));
     if (j > 0) {
@@ -271,12 +278,12 @@ __global__ void __launch_bounds__(kNT) k_lz_proj(const LanczosRun r, int j, int 
 
 // c_i = sum of the partials; w -= sum_{i<=j} c_i v_i, one element a thread; partial ||w||^2.
 __global__ void __launch_bounds__(kNT) k_lz_reorth(const LanczosRun r, int j) {
-    __shared__ double c[kMaxLanczosSteps];
+    constexpr int U = 20;
+    __shared__ double c[(kMaxLanczosSteps + U - 1) / U * U];   // read in whole chunks, past j without effect
     __shared__ double xs[4][64];
     const LzProblem q = problem_of(r, blockIdx.y);
     if (j >= q.k || (int)blockIdx.x >= 4 * q.nbv) return;
     const int n = (int)q.n, e = (int)slice_element(blockIdx.x), ec = e < n ? e : n - 1;
-    constexpr int U = 20;
     const int broken = q.L.state[0];
     double x = q.L.w[ec];
     double v[U];
@@ -292,13 +299,19 @@ __global__ void __launch_bounds__(kNT) k_lz_reorth(const LanczosRun r, int j) {
     if (broken) return;
     __syncthreads();
     for (int i0 = 0;; i0 += U) {
-        const int last = j - i0 < U - 1 ? j - i0 : U - 1;
+        const bool more = i0 + U <= j;
+        double ci[U], next[U];   // all LDS reads and the next chunk's loads first: a wait for each otherwise
+        if (more) {
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (u <= last) x = fma(-c[i0 + u], v[u], x);
-        if (i0 + U > j) break;
+            for (int u = 0; u < U; ++u) next[u] = V[(int64_t)(i0 + U + u < j ? i0 + U + u : j) * n];
+        }
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = V[(int64_t)(i0 + U + u < j ? i0 + U + u : j) * n];
+        for (int u = 0; u < U; ++u) ci[u] = c[i0 + u];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x = i0 + u <= j ? fma(-ci[u], v[u], x) : x;
+        if (!more) break;
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = next[u];
     }
     if (e < n) q.L.w[e] = x;
     norm_partial(e < n ? x : 0.0, xs, q.L.pn + blockIdx.x);
