@@ -428,7 +428,8 @@ k_batch_cform(const double* __restrict__ c, int order, int k, int m, double* __r
 }
 
 // ---- block sums R_l = sum_i e_{l,i} T_i (T_0 = I), all l of a problem in one pass, 16-byte vectors
-// on and above the diagonal's blocks of kUpper columns (padding included: zero in, zero out), rows in pairs
+// on and above the diagonal's blocks of kUpper columns (padding included, stored as zeros whatever the
+// coefficients: a problem without a bracket, or a scalar one, has NaN in them), rows in pairs
 // (y, n - 1 - y) as in k_combine.hip.  Threads take vectors of a problem in one sequence: rows of a
 // small problem do not fill a work-group.  The last block, the chain's first operand, is mirrored by
 // k_batch_mirror.  Whole calls, float32, 128 problems of 96..1024, order 256: 25.6 -> 24.9 ms, 64 of 96..512
@@ -482,7 +483,7 @@ k_batch_combine(const BatchGeom* __restrict__ geo, const double* __restrict__ co
             if (l < lcount) {
                 V o;
 #pragma unroll
-                for (int w = 0; w < W; ++w) o[w] = (T)acc[l][w];
+                for (int w = 0; w < W; ++w) o[w] = col + w < n ? (T)acc[l][w] : (T)0;
                 *reinterpret_cast<V*>(rb + (int64_t)(l0 + l) * stride + off) = o;
             }
         }
