@@ -384,6 +384,8 @@ int chebdm_block_coeffs(chebdm_handle h, const double* c, int32_t order, int32_t
  *   (chebdm_status of that problem), iters_out[p], trace_out[p] (tr D).
  *   Synchronises.  Returns the worst status (a negative one if any problem
  *   failed; the others are still valid).
+ * chebdm_batch_destroy may come after the handle's; every other call on a plan
+ *   needs its handle.
  * chebdm_batch_info: k, m, products per problem, (problem, tile) items per
  *   product step, algorithmic flops of all products of one run.
  */

@@ -36,6 +36,7 @@ int bucket_of(int64_t n) { return n <= 256 ? 0 : (n <= 512 ? 1 : (n <= 768 ? 2 :
 
 struct chebdm_batch_ctx {
     chebdm_handle h = nullptr;
+    int device = 0;
     hipStream_t bs = nullptr;      // own stream: graphs cannot be captured on the legacy stream
     hipEvent_t ready = nullptr;
     BatchDims d{};
@@ -354,6 +355,7 @@ int chebdm_batch_create(chebdm_handle h, int32_t count, const int64_t* n, int32_
     chebdm_batch_ctx* b = new (std::nothrow) chebdm_batch_ctx();
     if (!b) return fail(CHEBDM_ERR_OOM, "cannot allocate the batch plan");
     b->h = h;
+    b->device = h->device;
     b->elem = o.prec == CHEBDM_FP64 ? 8 : 4;
     b->tol = o.tol > 0.0 ? o.tol : 1e-10;
     b->max_iter = o.max_iter > 0 ? o.max_iter : 200;
@@ -469,7 +471,7 @@ int chebdm_batch_create(chebdm_handle h, int32_t count, const int64_t* n, int32_
 
 int chebdm_batch_destroy(chebdm_batch b) {
     if (!b) return CHEBDM_OK;
-    if (b->h) (void)hipSetDevice(b->h->device);
+    (void)hipSetDevice(b->device);   // the handle may be gone already
     if (b->bs) (void)hipStreamSynchronize(b->bs);
     drop_graph(b);
     if (b->items) (void)hipFree(b->items);

@@ -68,3 +68,15 @@ def test_batch_after_a_failed_problem(cd, prec, spoil):
         handle.close()
     for a, b in zip(*out):
         assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+def test_plan_destroyed_after_its_handle(cd):
+    # as when a collector frees both: the plan's destruction has to leave no error for the next launch
+    other = cd.Handle(0)
+    for _ in range(8):
+        handle = cd.Handle(0)
+        plan = cd.chebdm_batch_create(handle, [16, 33], 8)
+        handle.close()
+        plan.close()
+        assert np.isfinite(cd.chebdm_coeffs(other, 5.0, 0.1, -1.0, 1.0, 8)).all()
+    other.close()
