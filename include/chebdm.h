@@ -55,7 +55,11 @@ typedef struct chebdm_ctx* chebdm_handle;
 /* Arithmetic of the matrix products (the bounds, coefficients, traces,
  * moments and the mu search are always float64). */
 enum chebdm_prec {
-    CHEBDM_FP64 = 0,   /* float64 MFMA products, float64 matrices            */
+    CHEBDM_FP64 = 0,   /* float64 MFMA products, float64 matrices.  From n = */
+                       /* 960 on, where every row of H is spread out (see    */
+                       /* below), products go by residue arithmetic on the   */
+                       /* int8 units: operands in fixed point of 57 bits,    */
+                       /* products exact, then rounded to float64            */
     CHEBDM_FP32 = 1,   /* float32 MFMA products, float32 matrices            */
     CHEBDM_BF16X3 = 2, /* float32 matrices, products as three bfloat16 MFMA  */
                        /* terms hi*hi + hi*lo + lo*hi, float32 accumulation  */
@@ -64,6 +68,13 @@ enum chebdm_prec {
                        /* six MFMA terms down to 2^-16 (hh hm mh hl lh mm),  */
                        /* float32 accumulation: about float32 accuracy       */
 };
+
+/* Fixed-point products lose the digits of entries far below their row, so they are taken only for an H
+ * with (sum |h_ij|)^2 > (n - 1)/2 sum h_ij^2 over j != i in every row i (normal entries have 2/pi in place
+ * of the 1/2; a weakly coupled fragment, a band or a decaying row is below it) and sum |h_ij| at least an
+ * eighth of emax - emin.  The call looks while it waits for the device: always with bounds of its own, with
+ * given ones unless it is chebdm_density without info.  Other calls, and calls without the memory for the
+ * residue planes, take the float64 units; both are deterministic, their last digits differ. */
 
 /* Order of the baby-step products T_2..T_k and of the mu search's ladder T_2k, T_3k, ...
    (both orders give the same matrices up to rounding). */

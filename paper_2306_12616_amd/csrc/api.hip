@@ -89,6 +89,7 @@ struct Plan {
     size_t elem = 8;
     int n_gemm = 0;
     bool unit = false;   // Gershgorin's bounds: the spectrum of T_1 lies in [-1, 1], no T_i has a row norm above 1
+    bool dense = false;  // H's rows allow fixed-point operands (dense_rows)
 };
 
 }  // namespace
@@ -233,7 +234,7 @@ RnsLayout rns_layout(const Plan& pl) {
 int ensure_rns(chebdm_handle h, const Plan& pl) {
     const RnsLayout l = rns_layout(pl);
     h->rns_slots = 0;
-    if (l.slots == 0) return 0;
+    if (l.slots == 0 || !pl.dense) return 0;
     if (l.bytes > h->rns_bytes) {
         if (h->rns) {
             HIP_TRY(hipStreamSynchronize(h->stream));
@@ -387,24 +388,50 @@ int validate_matrix(const void* dH, int64_t n, int64_t ldh) {
 int lanczos_on_device(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, int steps, double margin,
                       uint64_t seed);
 
+// Whether float64 products of this H's matrices may be taken in fixed point (k_rns.hip), whose error in
+// entry (i, j) is about 2^-57 |a_i| |b_j| where a float64 sum has 2^-53 sum_k |a_ik b_kj|.  The first is the
+// smaller where that sum is a fair part of |a_i| |b_j|, and not where H has structure: two fragments
+// coupled by a factor of 1e-10 keep 16 digits of D's coupling block in float64, 6 of them in fixed point,
+// and entries below 2^-58 become zero.  So the rows of H have to be spread out: with
+// (sum |h|)^2 > c (n - 1) sum h^2 off the diagonal in every row, each row is within acos(sqrt(c)) of the
+// all-ones direction and sum_k |h_ik h_jk| > (2 c - 1) |h_i| |h_j| for any two; c = 1/2 is where two
+// rows could be apart.  Normal entries have 2/pi (at least 0.59 over n = 960 .. 5000 dense test matrices of
+// three spectra), two uncoupled halves 1/pi, a band of b entries b / n.  And the radius of every row
+// has to be a fair part of the half-width that scales it (0.80 to 0.93 of Gershgorin's, about 10 of the
+// spectrum's): a row that is nearly all diagonal has its other entries far below the scale.
+// For such H the largest error of D is 0.1 to 1.06 of the float64 units' (n = 960 .. 3000, orders 64 .. 1200,
+// either bounds), its root mean square off the diagonal 0.25 to 1.01.  The sums come with Gershgorin's pass
+// over H.
+bool dense_rows(const DevScalars& s, double emin, double emax) {
+    return s.spread > 0.5 && s.radius >= 0.25 * (0.5 * (emax - emin));
+}
+
 // Bounds: the caller's, or computed here (one read-back): Gershgorin's, then with
-// CHEBDM_BOUNDS_LANCZOS the Lanczos bounds inside them.
+// CHEBDM_BOUNDS_LANCZOS the Lanczos bounds inside them.  With a plan whose products could go to the
+// int8 units also pl->dense; for given bounds only where the call waits for the device anyway.
 int resolve_bounds(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, double& emin, double& emax,
-                   const Plan* pl = nullptr) {
-    if (std::isnan(emin) || std::isnan(emax)) {
+                   Plan* pl = nullptr, bool waits = true) {
+    const bool own = std::isnan(emin) || std::isnan(emax);
+    const bool spread = pl && rns_layout(*pl).slots > 0 && (own || waits);
+    if (!own && (!std::isfinite(emin) || !std::isfinite(emax) || emax < emin))
+        return fail(CHEBDM_ERR_ARG, "bounds must be finite with emin <= emax");
+    if (own || spread) {
         CHECK(ensure_small(h, 0));
-        HIP_TRY(launch_gershgorin(dH, n, ldh, h->partial, kPartialDoubles, h->scal, h->stream, h->h_scal));
-        if (pl && pl->bounds == CHEBDM_BOUNDS_LANCZOS) {
+        HIP_TRY(launch_gershgorin(dH, n, ldh, h->partial, kPartialDoubles, h->scal, h->stream, h->h_scal, spread));
+        if (own && pl && pl->bounds == CHEBDM_BOUNDS_LANCZOS) {
             CHECK(lanczos_on_device(h, dH, n, ldh, pl->lz_steps, pl->lz_margin, 0));
             CHECK(publish_scalars(h, nullptr, 0, 0));
         }
         HIP_TRY(hipStreamSynchronize(h->stream));
+    }
+    if (own) {
         if (h->h_scal->nonfinite) return fail(CHEBDM_ERR_NONFINITE, "H holds NaN or Inf");
         emin = h->h_scal->emin;
         emax = h->h_scal->emax;
+        if (!std::isfinite(emin) || !std::isfinite(emax) || emax < emin)
+            return fail(CHEBDM_ERR_ARG, "bounds must be finite with emin <= emax");
     }
-    if (!std::isfinite(emin) || !std::isfinite(emax) || emax < emin)
-        return fail(CHEBDM_ERR_ARG, "bounds must be finite with emin <= emax");
+    if (spread) pl->dense = dense_rows(*h->h_scal, emin, emax);
     return 0;
 }
 
@@ -1187,7 +1214,7 @@ int chebdm_density(chebdm_handle h, const double* dH, int64_t n, int64_t ldh, do
     CHECK(plan_split(pl));
     CHECK(set_device(h));
     pl.unit = bounds_dev && pl.bounds != CHEBDM_BOUNDS_LANCZOS;
-    CHECK(resolve_bounds(h, dH, n, ldh, emin, emax, &pl));
+    CHECK(resolve_bounds(h, dH, n, ldh, emin, emax, &pl, info != nullptr));
     pl.unit = pl.unit && wide_bounds(emin, emax);
     CHECK(ensure_small(h, 0));
     if (emax == emin) {

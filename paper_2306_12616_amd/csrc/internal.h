@@ -21,6 +21,8 @@ struct DevScalars {
     double n_elec;        // target electron count
     double tol;           // bisection tolerance
     double lo, hi;        // final bracket
+    double spread;        // min over the rows of H of (sum |h|)^2 / ((n - 1) sum h^2), off the diagonal
+    double radius;        // min over the rows of sum |h|, off the diagonal (both where asked for)
     int32_t nonfinite;    // H held NaN/Inf
     int32_t status;       // CHEBDM_OK / WARN_NOCONV / ERR_BRACKET
     int32_t iters;        // bisection sweeps
@@ -55,8 +57,10 @@ struct GemmBatch {
 };
 
 // ---- bounds / shift / traces (k_bounds.hip)
+// h_s: host mirror of what is written to *s; with_spread: spread and radius too
 hipError_t launch_gershgorin(const double* H, int64_t n, int64_t ldh, double* partial,
-                             int64_t partial_cap, DevScalars* s, hipStream_t st, DevScalars* h_s = nullptr);
+                             int64_t partial_cap, DevScalars* s, hipStream_t st, DevScalars* h_s = nullptr,
+                             bool with_spread = false);
 hipError_t launch_set_scalars(DevScalars* s, double emin, double emax, double beta, double mu,
                               int has_mu, double n_elec, double tol, int max_iter, hipStream_t st,
                               int bounds_on_device = 0);

@@ -18,6 +18,9 @@ namespace {
 
 constexpr int kColsPerBlock = 256;
 
+// SPREAD: also the columns' sums of squares off the diagonal, after the absolute sums in `partial`
+// (the pass reads H from memory either way).
+template <bool SPREAD>
 __global__ void __launch_bounds__(kColsPerBlock)
 k_gersh_partial(const double* __restrict__ H, int64_t n, int64_t ldh, int64_t rows_per_split,
                 double* __restrict__ partial) {
@@ -25,101 +28,172 @@ k_gersh_partial(const double* __restrict__ H, int64_t n, int64_t ldh, int64_t ro
     if (j >= n) return;
     const int64_t i0 = (int64_t)blockIdx.y * rows_per_split;
     const int64_t i1 = i0 + rows_per_split < n ? i0 + rows_per_split : n;
-    double s = 0.0;
+    double s = 0.0, q = 0.0;
     const double* p = H + i0 * ldh + j;
 #pragma unroll 8
     for (int64_t i = i0; i < i1; ++i, p += ldh) {
-        const double v = fabs(*p);
-        s += (i == j) ? 0.0 : v;
+        const double h = fabs(*p), v = (i == j) ? 0.0 : h;   // the load without a condition
+        s += v;
+        if constexpr (SPREAD) q = fma(v, v, q);
     }
     partial[(int64_t)blockIdx.y * n + j] = s;
+    if constexpr (SPREAD) partial[((int64_t)gridDim.y + blockIdx.y) * n + j] = q;
 }
 
 constexpr int kColThreads = 256;
 
-// Column j: r_j = sum of the split partials in order (sixteen loads in flight; one load per addition
-// took 20 us at N = 2000), the disc [d - r_j, d + r_j] with d = H[j][j].
-__device__ __forceinline__ void column_disc(const double* __restrict__ H, int64_t n, int64_t ldh,
-                                            const double* __restrict__ partial, int nsplit, int64_t j, double& lo,
-                                            double& hi, double& bad) {
-    double r = 0.0;
-    const double d = H[j * ldh + j];
+// Sums of a column's split partials in order (sixteen loads of each in flight; one load per addition
+// took 20 us at N = 2000): absolute values and, for SPREAD, squares.
+template <bool SPREAD>
+__device__ __forceinline__ void split_sums(const double* __restrict__ partial, int64_t n, int nsplit, int64_t j,
+                                           double& r, double& q) {
+    const double* squares = partial + (int64_t)nsplit * n;
+    r = q = 0.0;
     int sp = 0;
     for (; sp + 16 <= nsplit; sp += 16) {
-        double v[16];
+        double v[16], w[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = partial[(int64_t)(sp + u) * n + j];
+        for (int u = 0; u < 16; ++u) {
+            v[u] = partial[(int64_t)(sp + u) * n + j];
+            if constexpr (SPREAD) w[u] = squares[(int64_t)(sp + u) * n + j];
+        }
 #pragma unroll
-        for (int u = 0; u < 16; ++u) r += v[u];
+        for (int u = 0; u < 16; ++u) {
+            r += v[u];
+            if constexpr (SPREAD) q += w[u];
+        }
     }
-    for (; sp < nsplit; ++sp) r += partial[(int64_t)sp * n + j];
-    if (!isfinite(r) || !isfinite(d)) bad = 1.0;
-    lo = d - r;
-    hi = d + r;
+    for (; sp < nsplit; ++sp) {
+        r += partial[(int64_t)sp * n + j];
+        if constexpr (SPREAD) q += squares[(int64_t)sp * n + j];
+    }
 }
 
-// Per work-group of columns: min, max and a non-finite flag, written to out[3][nb].
+// What the columns' sums give, per column or over a set of them.
+struct Discs {
+    double lo = INFINITY, hi = -INFINITY, bad = 0.0, spread = INFINITY, radius = INFINITY;
+};
+
+// Column j: r_j = sum |h_ij| off the diagonal, the disc [d - r_j, d + r_j] with d = H[j][j].
+template <bool SPREAD>
+__device__ __forceinline__ Discs column_disc(const double* __restrict__ H, int64_t n, int64_t ldh,
+                                             const double* __restrict__ partial, int nsplit, int64_t j) {
+    Discs c;
+    const double d = H[j * ldh + j];
+    double r, q;
+    split_sums<SPREAD>(partial, n, nsplit, j, r, q);
+    if (!isfinite(r) || !isfinite(d)) c.bad = 1.0;
+    c.lo = d - r;
+    c.hi = d + r;
+    if constexpr (SPREAD) {
+        // zero where the sums leave the float64 range (a spread is at most 1 up to rounding)
+        const double v = r * r / ((double)(n - 1) * q);
+        c.spread = q >= 1e-290 && v < 2.0 ? v : 0.0;
+        c.radius = r >= 0.0 ? r : 0.0;
+    }
+    return c;
+}
+
+template <int NT, bool SPREAD>
+__device__ __forceinline__ void reduce_discs(Discs& c, double* smem) {
+    c.bad = block_sum<NT>(c.bad, smem);
+    c.lo = block_min<NT>(c.lo, smem);
+    c.hi = block_max<NT>(c.hi, smem);
+    if constexpr (SPREAD) {
+        c.spread = block_min<NT>(c.spread, smem);
+        c.radius = block_min<NT>(c.radius, smem);
+    }
+}
+
+// Per work-group of columns: min, max, a non-finite flag and the spread's minima, written to out[5][nb].
+template <bool SPREAD>
 __global__ void __launch_bounds__(kColThreads)
 k_gersh_cols(const double* __restrict__ H, int64_t n, int64_t ldh, const double* __restrict__ partial, int nsplit,
              double* __restrict__ out, int nb) {
     __shared__ double smem[kColThreads / 64];
     const int64_t j = (int64_t)blockIdx.x * kColThreads + threadIdx.x;
-    double lo = INFINITY, hi = -INFINITY, bad = 0.0;
-    if (j < n) column_disc(H, n, ldh, partial, nsplit, j, lo, hi, bad);
-    bad = block_sum<kColThreads>(bad, smem);
-    lo = block_min<kColThreads>(lo, smem);
-    hi = block_max<kColThreads>(hi, smem);
+    Discs c;
+    if (j < n) c = column_disc<SPREAD>(H, n, ldh, partial, nsplit, j);
+    reduce_discs<kColThreads, SPREAD>(c, smem);
     if (threadIdx.x == 0) {
-        out[blockIdx.x] = lo;
-        out[nb + blockIdx.x] = hi;
-        out[2 * nb + blockIdx.x] = bad;
+        out[blockIdx.x] = c.lo;
+        out[nb + blockIdx.x] = c.hi;
+        out[2 * nb + blockIdx.x] = c.bad;
+        if constexpr (SPREAD) {
+            out[3 * nb + blockIdx.x] = c.spread;
+            out[4 * nb + blockIdx.x] = c.radius;
+        }
     }
 }
 
 // The bounds into the scalars, and into their host mirror where one is given.
-__device__ __forceinline__ void put_bounds(DevScalars* s, double lo, double hi, int bad) {
+template <bool SPREAD>
+__device__ __forceinline__ void put_bounds(DevScalars* s, const Discs& c) {
     if (!s) return;
-    s->emin = lo;
-    s->emax = hi;
-    s->nonfinite = bad;
+    s->emin = c.lo;
+    s->emax = c.hi;
+    s->nonfinite = c.bad > 0.0 ? 1 : 0;
+    if constexpr (SPREAD) {
+        s->spread = c.spread;
+        s->radius = c.radius;
+    }
 }
 
 // Up to kOneFold columns: columns and result in one launch.
 constexpr int kOneFold = 1024;
 
+template <bool SPREAD>
 __global__ void __launch_bounds__(kOneFold)
 k_gersh_fold(const double* __restrict__ H, int64_t n, int64_t ldh, const double* __restrict__ partial, int nsplit,
              DevScalars* s, DevScalars* h_s) {
     __shared__ double smem[kOneFold / 64];
-    double lo = INFINITY, hi = -INFINITY, bad = 0.0;
-    if ((int)threadIdx.x < n) column_disc(H, n, ldh, partial, nsplit, threadIdx.x, lo, hi, bad);
-    bad = block_sum<kOneFold>(bad, smem);
-    lo = block_min<kOneFold>(lo, smem);
-    hi = block_max<kOneFold>(hi, smem);
+    Discs c;
+    if ((int)threadIdx.x < n) c = column_disc<SPREAD>(H, n, ldh, partial, nsplit, threadIdx.x);
+    reduce_discs<kOneFold, SPREAD>(c, smem);
     if (threadIdx.x == 0) {
-        put_bounds(s, lo, hi, bad > 0.0 ? 1 : 0);
-        put_bounds(h_s, lo, hi, bad > 0.0 ? 1 : 0);
+        put_bounds<SPREAD>(s, c);
+        put_bounds<SPREAD>(h_s, c);
     }
 }
 
 constexpr int kFinalThreads = 256;
 
+template <bool SPREAD>
 __global__ void __launch_bounds__(kFinalThreads)
 k_gersh_final(const double* __restrict__ part, int nb, DevScalars* s, DevScalars* h_s) {
     __shared__ double smem[kFinalThreads / 64];
-    double lo = INFINITY, hi = -INFINITY, bad = 0.0;
+    Discs c;
     for (int b = threadIdx.x; b < nb; b += kFinalThreads) {
-        lo = fmin(lo, part[b]);
-        hi = fmax(hi, part[nb + b]);
-        bad += part[2 * nb + b];
+        c.lo = fmin(c.lo, part[b]);
+        c.hi = fmax(c.hi, part[nb + b]);
+        c.bad += part[2 * nb + b];
+        if constexpr (SPREAD) {
+            c.spread = fmin(c.spread, part[3 * nb + b]);
+            c.radius = fmin(c.radius, part[4 * nb + b]);
+        }
     }
-    bad = block_sum<kFinalThreads>(bad, smem);
-    lo = block_min<kFinalThreads>(lo, smem);
-    hi = block_max<kFinalThreads>(hi, smem);
+    reduce_discs<kFinalThreads, SPREAD>(c, smem);
     if (threadIdx.x == 0) {
-        put_bounds(s, lo, hi, bad > 0.0 ? 1 : 0);
-        put_bounds(h_s, lo, hi, bad > 0.0 ? 1 : 0);
+        put_bounds<SPREAD>(s, c);
+        put_bounds<SPREAD>(h_s, c);
     }
+}
+
+template <bool SPREAD>
+void gershgorin(const double* H, int64_t n, int64_t ldh, double* partial, int64_t nsplit, int64_t rows_per_split,
+                DevScalars* s, DevScalars* h_s, hipStream_t st) {
+    const int64_t col_blocks = (n + kColsPerBlock - 1) / kColsPerBlock, nb = (n + kColThreads - 1) / kColThreads;
+    double* part2 = partial + (SPREAD ? 2 : 1) * nsplit * n;
+    hipLaunchKernelGGL(k_gersh_partial<SPREAD>, dim3((unsigned)col_blocks, (unsigned)nsplit), dim3(kColsPerBlock), 0, st,
+                       H, n, ldh, rows_per_split, partial);
+    if (n <= kOneFold) {
+        hipLaunchKernelGGL(k_gersh_fold<SPREAD>, dim3(1), dim3(kOneFold), 0, st, H, n, ldh, (const double*)partial,
+                           (int)nsplit, s, h_s);
+        return;
+    }
+    hipLaunchKernelGGL(k_gersh_cols<SPREAD>, dim3((unsigned)nb), dim3(kColThreads), 0, st, H, n, ldh,
+                       (const double*)partial, (int)nsplit, part2, (int)nb);
+    hipLaunchKernelGGL(k_gersh_final<SPREAD>, dim3(1), dim3(kFinalThreads), 0, st, (const double*)part2, (int)nb, s, h_s);
 }
 
 // T_1 = H~ = (H - cen I) / half; only the n x n part is written.
@@ -209,29 +283,19 @@ hipError_t launch_copy_out(const void* src, int is_f64, int64_t ld, int64_t n, d
 }
 
 hipError_t launch_gershgorin(const double* H, int64_t n, int64_t ldh, double* partial,
-                             int64_t partial_cap, DevScalars* s, hipStream_t st, DevScalars* h_s) {
+                             int64_t partial_cap, DevScalars* s, hipStream_t st, DevScalars* h_s, bool with_spread) {
     const int64_t col_blocks = (n + kColsPerBlock - 1) / kColsPerBlock;
     int64_t nsplit = (2048 + col_blocks - 1) / col_blocks;
     const int64_t max_split = (n + 31) / 32;
     if (nsplit > max_split) nsplit = max_split;
     if (nsplit < 1) nsplit = 1;
-    const int64_t nb = (n + kColThreads - 1) / kColThreads;
-    while (nsplit > 1 && nsplit * n + 3 * nb > partial_cap) nsplit >>= 1;
-    if (nsplit * n + 3 * nb > partial_cap) return hipErrorInvalidValue;
+    const int64_t nb = (n + kColThreads - 1) / kColThreads, per = with_spread ? 2 * n : n;
+    while (nsplit > 1 && nsplit * per + 5 * nb > partial_cap) nsplit >>= 1;
+    if (nsplit * per + 5 * nb > partial_cap) return hipErrorInvalidValue;
     const int64_t rows_per_split = (n + nsplit - 1) / nsplit;
     nsplit = (n + rows_per_split - 1) / rows_per_split;
-    double* part2 = partial + nsplit * n;
-    hipLaunchKernelGGL(k_gersh_partial, dim3((unsigned)col_blocks, (unsigned)nsplit), dim3(kColsPerBlock),
-                       0, st, H, n, ldh, rows_per_split, partial);
-    if (n <= kOneFold) {
-        hipLaunchKernelGGL(k_gersh_fold, dim3(1), dim3(kOneFold), 0, st, H, n, ldh, (const double*)partial, (int)nsplit,
-                           s, h_s);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(k_gersh_cols, dim3((unsigned)nb), dim3(kColThreads), 0, st, H, n, ldh,
-                       (const double*)partial, (int)nsplit, part2, (int)nb);
-    hipLaunchKernelGGL(k_gersh_final, dim3(1), dim3(kFinalThreads), 0, st, (const double*)part2, (int)nb, s,
-                       h_s);
+    if (with_spread) gershgorin<true>(H, n, ldh, partial, nsplit, rows_per_split, s, h_s, st);
+    else gershgorin<false>(H, n, ldh, partial, nsplit, rows_per_split, s, h_s, st);
     return hipGetLastError();
 }
 

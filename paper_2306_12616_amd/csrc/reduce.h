@@ -5,10 +5,10 @@
 
 namespace chebdm {
 
-// The butterfly v[l] + v[l ^ off] for off = 32, 16, 8, 4, 2, 1, every lane receiving the sum, without
+// The butterfly op(v[l], v[l ^ off]) for off = 32, 16, 8, 4, 2, 1, every lane receiving the result, without
 // LDS: the first two steps by lane-half and row swaps, then DPP rotations inside the rows of 16
 // (after a step the values repeat with period off, so lane l + off / 2 holds what l ^ (off / 2) does).
-// Same additions, same bits as with __shfl_xor, at a fraction of the latency.
+// Same operations, same bits as with __shfl_xor, at a fraction of the latency.
 template <int N>
 __device__ __forceinline__ double row_rotate(double v) {
     const uint64_t u = __builtin_bit_cast(uint64_t, v);
@@ -17,37 +17,36 @@ __device__ __forceinline__ double row_rotate(double v) {
     return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
+template <class Op>
+__device__ __forceinline__ double wave_reduce(double v, Op op) {
     {
         const uint64_t u = __builtin_bit_cast(uint64_t, v);
         const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
         const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
-        v = __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
-            __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+        v = op(__builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]),
+               __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]));
     }
     {
         const uint64_t u = __builtin_bit_cast(uint64_t, v);
         const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
         const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
-        v = __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
-            __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+        v = op(__builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]),
+               __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]));
     }
-    v += row_rotate<8>(v);
-    v += row_rotate<4>(v);
-    v += row_rotate<2>(v);
-    return v + row_rotate<1>(v);
+    v = op(v, row_rotate<8>(v));
+    v = op(v, row_rotate<4>(v));
+    v = op(v, row_rotate<2>(v));
+    return op(v, row_rotate<1>(v));
 }
 
-__device__ inline double wave_min(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off, 64));
-    return v;
+__device__ __forceinline__ double wave_sum(double v) {
+    return wave_reduce(v, [](double a, double b) { return a + b; });
 }
-
-__device__ inline double wave_max(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-    return v;
+__device__ __forceinline__ double wave_min(double v) {
+    return wave_reduce(v, [](double a, double b) { return fmin(a, b); });
+}
+__device__ __forceinline__ double wave_max(double v) {
+    return wave_reduce(v, [](double a, double b) { return fmax(a, b); });
 }
 
 // Sum over a workgroup of NT threads; every thread receives the result.
