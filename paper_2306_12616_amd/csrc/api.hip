@@ -30,6 +30,29 @@ int fail(int code, const std::string& msg) {
     return code;
 }
 
+// The planes go back (the free waits for the work that uses them).
+hipError_t release_planes(chebdm_handle h) {
+    const hipError_t e = h->rns ? hipFree(h->rns) : hipSuccess;
+    h->rns = nullptr;
+    h->rns_bytes = 0;
+    h->rns_slots = 0;
+    return e;
+}
+
+hipError_t device_alloc(chebdm_handle h, void** p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess && h->rns) {
+        (void)hipGetLastError();
+        e = release_planes(h);
+        if (e == hipSuccess) e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) {
+        *p = nullptr;
+        (void)hipGetLastError();
+    }
+    return e;
+}
+
 // Opens a timed region on the handle's stream (no-op unless profiling is on).
 int prof_begin(chebdm_handle h, int kind, int products, double flop, double bytes, size_t* idx) {
     *idx = (size_t)-1;
@@ -118,10 +141,8 @@ int ensure_small(chebdm_handle h, int64_t M) {
     const int64_t Mcap = M < 4096 ? 4096 : M;
     const size_t bytes = small_bytes_for(M);
     void* fresh = nullptr;
-    if (hipMalloc(&fresh, bytes) != hipSuccess) {
-        (void)hipGetLastError();
+    if (device_alloc(h, &fresh, bytes) != hipSuccess)
         return fail(CHEBDM_ERR_OOM, "cannot allocate " + std::to_string(bytes) + " bytes of scalar workspace");
-    }
     if (h->small) {
         HIP_TRY(hipMemcpyAsync(fresh, h->small, 64 * sizeof(double), hipMemcpyDeviceToDevice, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
@@ -155,31 +176,14 @@ int ensure_mats(chebdm_handle h, const Plan& pl, int64_t count) {
             h->mats = nullptr;
             h->mats_bytes = 0;
         }
-        hipError_t e = hipMalloc(&h->mats, bytes);
-        if (e != hipSuccess && h->rns) {   // the residue planes of earlier calls are only a faster route
-            (void)hipGetLastError();
-            HIP_TRY(hipStreamSynchronize(h->stream));
-            HIP_TRY(hipFree(h->rns));
-            h->rns = nullptr;
-            h->rns_bytes = 0;
-            e = hipMalloc(&h->mats, bytes);
-        }
-        if (e != hipSuccess) {
-            h->mats = nullptr;
-            (void)hipGetLastError();
+        if (device_alloc(h, &h->mats, bytes) != hipSuccess)
             return fail(CHEBDM_ERR_OOM, "cannot allocate " + std::to_string(bytes) + " bytes of matrix workspace");
-        }
         h->mats_bytes = bytes;
         h->lay_ld = -1;
     }
     // partial accumulators of K-sliced tail tiles of the products
-    if (!h->gemm_scratch) {
-        if (hipMalloc(&h->gemm_scratch, kGemmScratchBytes) != hipSuccess) {
-            h->gemm_scratch = nullptr;
-            (void)hipGetLastError();
-            return fail(CHEBDM_ERR_OOM, "cannot allocate the product scratch");
-        }
-    }
+    if (!h->gemm_scratch && device_alloc(h, &h->gemm_scratch, kGemmScratchBytes) != hipSuccess)
+        return fail(CHEBDM_ERR_OOM, "cannot allocate the product scratch");
     // The kernels rely on a zero padding outside each n x n block; a new
     // layout (n, leading dimension, element size or a larger count) is cleared once.
     if (h->lay_n != pl.n || h->lay_ld != pl.ld || h->lay_elem != pl.elem || h->lay_count < count) {
@@ -236,12 +240,7 @@ int ensure_rns(chebdm_handle h, const Plan& pl) {
     h->rns_slots = 0;
     if (l.slots == 0 || !pl.dense) return 0;
     if (l.bytes > h->rns_bytes) {
-        if (h->rns) {
-            HIP_TRY(hipStreamSynchronize(h->stream));
-            HIP_TRY(hipFree(h->rns));
-            h->rns = nullptr;
-            h->rns_bytes = 0;
-        }
+        HIP_TRY(release_planes(h));
         if (hipMalloc(&h->rns, l.bytes) != hipSuccess) {
             h->rns = nullptr;
             (void)hipGetLastError();
@@ -759,11 +758,8 @@ int ensure_lanczos(chebdm_handle h, int64_t n, int steps) {
     if (h->lz) HIP_TRY(hipFree(h->lz));
     h->lz = nullptr;
     h->lz_doubles = 0;
-    if (hipMalloc(&h->lz, sizeof(double) * (size_t)need) != hipSuccess) {
-        h->lz = nullptr;
-        (void)hipGetLastError();
+    if (device_alloc(h, (void**)&h->lz, sizeof(double) * (size_t)need) != hipSuccess)
         return fail(CHEBDM_ERR_OOM, "cannot allocate the Lanczos workspace");
-    }
     h->lz_doubles = need;
     return 0;
 }
@@ -1078,7 +1074,7 @@ int chebdm_destroy(chebdm_handle h) {
     if (h->small) (void)hipFree(h->small);
     if (h->lz) (void)hipFree(h->lz);
     if (h->gemm_scratch) (void)hipFree(h->gemm_scratch);
-    if (h->rns) (void)hipFree(h->rns);
+    (void)release_planes(h);
     if (h->mlp_work) (void)hipFree(h->mlp_work);
     if (h->h_scal) (void)hipHostFree(h->h_scal);
     delete h;

@@ -132,7 +132,7 @@ int upload_schedule(chebdm_batch_ctx* b) {
     b->nitems = (int)items.size();
     if (b->items) HIP_TRY(hipFree(b->items));
     b->items = nullptr;
-    HIP_TRY(hipMalloc(&b->items, sizeof(TileItem) * items.size()));
+    HIP_TRY(device_alloc(b->h, (void**)&b->items, sizeof(TileItem) * items.size()));
     HIP_TRY(hipMemcpy(b->items, items.data(), sizeof(TileItem) * items.size(), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(b->geo, geo.data(), sizeof(BatchGeom) * count, hipMemcpyHostToDevice));
     drop_graph(b);
@@ -388,18 +388,12 @@ int chebdm_batch_create(chebdm_handle h, int32_t count, const int64_t* n, int32_
         b->lz_margin = o.bounds_margin > 0.0 ? o.bounds_margin : 0.01;
         b->lz_stride = (lanczos_work_doubles(nmax, b->lz_steps) + 31) / 32 * 32;
         const size_t lz_bytes = sizeof(double) * (size_t)b->lz_stride * (size_t)count;
-        if (hipMalloc(&b->lz, lz_bytes) != hipSuccess) {
-            b->lz = nullptr;
-            (void)hipGetLastError();
+        if (device_alloc(h, (void**)&b->lz, lz_bytes) != hipSuccess)
             return bail(fail(CHEBDM_ERR_OOM, "cannot allocate " + std::to_string(lz_bytes) + " bytes of Lanczos workspace"));
-        }
     }
     b->mats_bytes = (size_t)tot * b->elem;
-    if (hipMalloc(&b->mats, b->mats_bytes) != hipSuccess) {
-        b->mats = nullptr;
-        (void)hipGetLastError();
+    if (device_alloc(h, &b->mats, b->mats_bytes) != hipSuccess)
         return bail(fail(CHEBDM_ERR_OOM, "cannot allocate " + std::to_string(b->mats_bytes) + " bytes of batch workspace"));
-    }
     // small buffers in one allocation
     const size_t L1 = (size_t)order + 1, K = (size_t)k, M = (size_t)m, C = (size_t)count;
     int64_t ncols = 0;
@@ -420,11 +414,8 @@ int chebdm_batch_create(chebdm_handle h, int32_t count, const int64_t* n, int32_
     const size_t o_c = take(sizeof(double) * C * L1), o_coef = take(sizeof(double) * C * K * M);
     const size_t o_mu = take(sizeof(double) * C), o_trd = take(sizeof(double) * C);
     const size_t o_feat = take(sizeof(float) * C * 64), o_muh = take(sizeof(float) * C);
-    if (hipMalloc(&b->dev, bytes) != hipSuccess) {
-        b->dev = nullptr;
-        (void)hipGetLastError();
+    if (device_alloc(h, &b->dev, bytes) != hipSuccess)
         return bail(fail(CHEBDM_ERR_OOM, "cannot allocate " + std::to_string(bytes) + " bytes of batch tables"));
-    }
     char* base = static_cast<char*>(b->dev);
     b->geo = (BatchGeom*)(base + o_geo);
     b->tab = (BatchProblem*)(base + o_tab);

@@ -16,11 +16,8 @@ int ensure_mlp_work(chebdm_handle h, int64_t floats) {
         HIP_TRY(hipFree(h->mlp_work));
         h->mlp_work = nullptr;
     }
-    if (hipMalloc((void**)&h->mlp_work, sizeof(float) * (size_t)floats) != hipSuccess) {
-        h->mlp_work = nullptr;
-        (void)hipGetLastError();
+    if (device_alloc(h, (void**)&h->mlp_work, sizeof(float) * (size_t)floats) != hipSuccess)
         return fail(CHEBDM_ERR_OOM, "cannot allocate the network workspace");
-    }
     h->mlp_work_floats = floats;
     return 0;
 }

@@ -68,6 +68,10 @@ struct chebdm_ctx {
 
 namespace chebdm {
 
+// hipMalloc for anything a call through the handle needs.  The residue planes of earlier calls are only a
+// faster route: where memory is short they are given back first.  On failure *p is null.
+hipError_t device_alloc(chebdm_handle h, void** p, size_t bytes);
+
 // Sets the thread-local message of chebdm_last_error and returns code.
 int fail(int code, const std::string& msg);
 
