@@ -332,8 +332,10 @@ int chebdm_mu_search(chebdm_handle h, const double* dH, int64_t n, int64_t ldh,
  * with ld = round_up(n, 128) and 8 (float64) or 4 bytes per element, plus the
  * small buffers sized for opts->n_quad quadrature nodes (2^16 when 0), plus
  * 96 MB of product scratch (partial sums of K-sliced product tiles).
- * Float64 calls from n = 960 on also hold residue planes of their operands
- * (at most 8.5 GB) where there is memory for them; they are not in the size.
+ * Not in the size: float64 calls from n = 960 up to 13760 whose H allows fixed-point products also hold
+ * residue planes, up to 12 sets of about 15 n^2 bytes and 256 MB (or one product's 7.5 n^2 bytes) of residues:
+ * 3 GB at n = 4000, at most 8 GiB of sets, 9.4 GiB in all.  They take no more than a quarter of the memory
+ * that is free when they grow, and go back when an allocation of the handle or its plans needs the room.
  * Needs no device; h may be NULL.  ERR_ARG on bad sizes or options.
  */
 int chebdm_workspace_size(chebdm_handle h, int64_t n, int32_t order, const chebdm_opts* opts,

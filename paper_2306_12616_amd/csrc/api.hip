@@ -204,7 +204,6 @@ struct RnsLayout {
     RnsGeom geo;
     int slots;
     int64_t set_stride, products;
-    size_t bytes;
 };
 
 // Where float64 products run on the int8 units: launches of at least two products from N = 960, single
@@ -219,37 +218,54 @@ struct RnsLayout {
 constexpr int64_t kRnsMinN = 960, kRnsSingleN = 1400;
 bool rns_pays(int64_t n) { return n >= kRnsMinN && (n <= 1024 || n > 1056); }
 
-// slots == 0: float64 units.  The operand sets take at most 8 GB (12 sets up to N = 6600; below
-// three the products would convert operands over and over, and the float64 units stay).
+// slots == 0: float64 units.  The operand sets take at most 8 GiB (12 sets up to N = 6600; below
+// three, from N = 13761, the products would convert operands over and over, and the float64 units stay).
+constexpr int kRnsMinSlots = 3, kRnsMaxSlots = 12;
 RnsLayout rns_layout(const Plan& pl) {
     RnsLayout l{};
     if (pl.prec != CHEBDM_FP64 || !rns_pays(pl.n)) return l;
     l.geo = rns_geom(pl.n);
     l.set_stride = l.geo.set_bytes + 2 * l.geo.rows * (int64_t)sizeof(double);
     const int64_t fit = ((int64_t)8 << 30) / l.set_stride;
-    if (fit < 3) return l;
-    l.slots = (int)std::min<int64_t>(fit, 12);
+    if (fit < kRnsMinSlots) return l;
+    l.slots = (int)std::min<int64_t>(fit, kRnsMaxSlots);
     l.products = std::max<int64_t>(1, std::min<int64_t>(kRnsGroup, ((int64_t)256 << 20) / l.geo.res_bytes));
-    l.bytes = (size_t)(l.slots * l.set_stride + l.products * l.geo.res_bytes);
     return l;
 }
+// Sets that fit `bytes` beside the residues.
+int rns_fit(const RnsLayout& l, size_t bytes) {
+    const int64_t sets = ((int64_t)bytes - l.products * l.geo.res_bytes) / l.set_stride;
+    return (int)std::min<int64_t>(std::max<int64_t>(sets, 0), l.slots);
+}
+size_t rns_bytes(const RnsLayout& l, int slots) {
+    return (size_t)(slots * l.set_stride + l.products * l.geo.res_bytes);
+}
 
-// Residue planes for the call's products; without the memory for them the float64 units do them.
+// Residue planes for the call's products.  They leave three quarters of the free memory to others: on a
+// fuller device the call has fewer sets (conversions are repeated, the bits are the same), and with room for
+// fewer than three the float64 units do the products.
 int ensure_rns(chebdm_handle h, const Plan& pl) {
     const RnsLayout l = rns_layout(pl);
     h->rns_slots = 0;
     if (l.slots == 0 || !pl.dense) return 0;
-    if (l.bytes > h->rns_bytes) {
-        HIP_TRY(release_planes(h));
-        if (hipMalloc(&h->rns, l.bytes) != hipSuccess) {
-            h->rns = nullptr;
-            (void)hipGetLastError();
-            return 0;
+    if (rns_fit(l, h->rns_bytes) < l.slots) {
+        size_t free = 0, total = 0;
+        HIP_TRY(hipMemGetInfo(&free, &total));
+        const int slots = rns_fit(l, (free + h->rns_bytes) / 4);
+        if (slots >= kRnsMinSlots && rns_bytes(l, slots) > h->rns_bytes) {
+            HIP_TRY(release_planes(h));
+            if (hipMalloc(&h->rns, rns_bytes(l, slots)) != hipSuccess) {
+                h->rns = nullptr;
+                (void)hipGetLastError();
+                return 0;
+            }
+            h->rns_bytes = rns_bytes(l, slots);
         }
-        h->rns_bytes = l.bytes;
     }
+    const int slots = rns_fit(l, h->rns_bytes);
+    if (slots < kRnsMinSlots) return 0;
     h->rns_geo = l.geo;
-    h->rns_slots = l.slots;
+    h->rns_slots = slots;
     h->rns_res_products = l.products;
     return 0;
 }
@@ -638,7 +654,7 @@ int odd_chain_step(int K) {
 // kernel argument of their sequences agrees, and the first call's graph can be replayed.
 struct ReplayKey {
     int32_t kind, order, k, m, prec, form, baby, ladder, search, max_iter, bounds_on_device, unit, sum, damping, split_h,
-        split_q;
+        split_q, rns_slots, pad;
     int64_t n, ld, ldh, ldd, M;
     const void *dH, *dD, *mats, *small, *rns;   // rns: null when the products run on the float64 units
     double tol, beta, x, emin, emax;   // x: n_elec (mu search) or mu (density)
@@ -675,6 +691,7 @@ std::vector<char> replay_key(int kind, const Plan& pl, chebdm_handle h, const do
     k.mats = h->mats;
     k.small = h->small;
     k.rns = h->rns_slots > 0 ? h->rns : nullptr;
+    k.rns_slots = h->rns_slots;
     k.tol = pl.tol;
     k.beta = beta;
     k.x = x;
