@@ -428,9 +428,9 @@ k_batch_cform(const double* __restrict__ c, int order, int k, int m, double* __r
 }
 
 // ---- block sums R_l = sum_i e_{l,i} T_i (T_0 = I), all l of a problem in one pass, 16-byte vectors
-// on and above the diagonal's blocks of kUpper columns (padding included, stored as zeros whatever the
-// coefficients: a problem without a bracket, or a scalar one, has NaN in them), rows in pairs
-// (y, n - 1 - y) as in k_combine.hip.  Threads take vectors of a problem in one sequence: rows of a
+// on and above the diagonal's blocks of kUpper columns, rows in pairs
+// (y, n - 1 - y) as in k_combine.hip; the padding stays zero (a problem without a bracket, or a scalar
+// one, has NaN coefficients, and 0 * NaN would stay there).  Threads take vectors of a problem in one sequence: rows of a
 // small problem do not fill a work-group.  The last block, the chain's first operand, is mirrored by
 // k_batch_mirror.  Whole calls, float32, 128 problems of 96..1024, order 256: 25.6 -> 24.9 ms, 64 of 96..512
 // 4.13 -> 3.99, 8 of 96..256, order 64 845 -> 848 us; float64, 32 of 96..1024, order 128: 7.82 -> 7.64 ms.
@@ -454,13 +454,14 @@ k_batch_combine(const BatchGeom* __restrict__ geo, const double* __restrict__ co
     const uint32_t length = (uint32_t)(2 * ld - n + 2 * kUpper) / W;   // vectors of a pair of rows, at most
     const uint32_t total = length * (uint32_t)((n + 1) / 2);
     for (uint32_t v = blockIdx.x * 256 + threadIdx.x; v < total; v += gridDim.x * 256) {
-        int64_t row = v / length, col = (int64_t)(v % length) * W + row / kUpper * kUpper;
-        if (col >= ld) {
-            const int64_t other = n - 1 - row;
-            col = other > row ? col - ld + other / kUpper * kUpper : ld;
+        int row = (int)(v / length), col = (int)(v % length) * W + row / kUpper * kUpper;
+        if (col >= (int)ld) {
+            const int other = (int)n - 1 - row;
+            col = other > row ? col - (int)ld + other / kUpper * kUpper : (int)ld;
             row = other;
         }
-        if (col >= ld) continue;
+        if (col >= (int)n) continue;
+        const bool whole = col + W <= (int)n;   // else n % W columns
         const int64_t off = row * ld + col;
         double acc[MB][W];
 #pragma unroll
@@ -483,7 +484,7 @@ k_batch_combine(const BatchGeom* __restrict__ geo, const double* __restrict__ co
             if (l < lcount) {
                 V o;
 #pragma unroll
-                for (int w = 0; w < W; ++w) o[w] = col + w < n ? (T)acc[l][w] : (T)0;
+                for (int w = 0; w < W; ++w) o[w] = whole || w < n % W ? (T)acc[l][w] : (T)0;
                 *reinterpret_cast<V*>(rb + (int64_t)(l0 + l) * stride + off) = o;
             }
         }

@@ -7,9 +7,9 @@
 // streams two elements of one row of every T_i once and keeps up to 24 float64
 // block accumulators per element in registers (four wavefronts per SIMD in
 // both precisions); T_0 = I adds coef[l][0] on the diagonal.
-// Full padded rows are processed and the padding of R_l is stored as zeros, whatever the coefficients:
-// a search that finds no bracket leaves NaN in them, and 0 * NaN in the padding would stay in the
-// workspace for later calls (products write only the n x n blocks).
+// The padding of R_l stays zero, whatever the coefficients: a search that finds no
+// bracket leaves NaN in them, and 0 * NaN in the padding would stay in the workspace for later calls (products
+// write only the n x n blocks).
 //
 // Upper form: all matrices are exactly symmetric and the giant steps read a block as an addend on and
 // above the diagonal only, so each row starts at its diagonal block of kUpper columns; the few
@@ -66,7 +66,7 @@ k_combine(const T* __restrict__ tbase, int64_t stride, int k, int l0, int lcount
             row = other;
         }
     }
-    const bool live = col < ld;
+    const bool live = col < n, whole = col + W <= n;   // else n % W columns
     const int64_t off = row * ld + (live ? col : 0);
     auto tload = [&](int j) { return *reinterpret_cast<const V*>(tbase + (int64_t)j * stride + off); };
     V t{};
@@ -112,7 +112,7 @@ k_combine(const T* __restrict__ tbase, int64_t stride, int k, int l0, int lcount
         if (l < lcount) {
             V o;
 #pragma unroll
-            for (int w = 0; w < W; ++w) o[w] = col + w < n ? (T)acc[l][w] : (T)0;
+            for (int w = 0; w < W; ++w) o[w] = whole || w < n % W ? (T)acc[l][w] : (T)0;
             *reinterpret_cast<V*>(rbase + (int64_t)(l0 + l) * stride + off) = o;
         }
     }
