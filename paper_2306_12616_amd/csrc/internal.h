@@ -101,7 +101,7 @@ hipError_t launch_lanczos(const double* H, int64_t n, int64_t ldh, int steps, do
                           double* work, DevScalars* s, hipStream_t st);
 
 // ---- coefficients / decomposition / moments / bisection (k_cheb.hip)
-// terms: 1 for the reduced forms, a cospi per term of the transforms (k_cheb.hip)
+// terms: 1 for the reduced forms, a cospi per term of the transforms (cheb_dev.h); so with M no power of two
 hipError_t launch_fermi_coeffs(int order, int M, const DevScalars* s, double* f_tab, double* c_out,
                                hipStream_t st, int damping = 0, int terms = 0);
 // split_h > 0: composition-form blocks rearranged for two Clenshaw chains split at h (m - h <= h);

@@ -399,7 +399,7 @@ k_batch_dct2(const int64_t* __restrict__ mq, int64_t mcap, const double* __restr
     const int p = blockIdx.y;
     const int64_t n = blockIdx.x, M = mq[p];
     const double* fp = f + p * mcap;
-    const double acc = block_sum<256>(TERMS ? dct2_terms(n, M, fp) : dct2_turned(n, M, fp), smem);
+    const double acc = block_sum<256>(dct2<TERMS>(n, M, fp), smem);
     if (threadIdx.x == 0)
         c[(int64_t)p * (order + 1) + n] = (n == 0 ? 1.0 : 2.0) * acc / (double)M * damping_factor(damping, (int)n, order);
 }

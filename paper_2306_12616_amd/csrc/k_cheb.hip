@@ -52,14 +52,14 @@ k_fermi_table(int64_t M, const DevScalars* __restrict__ s, double* __restrict__ 
 }
 
 // One workgroup per coefficient n: c_n = (2 - delta_{n0})/M sum_j f_j cos(n theta_j).  Order 512,
-// M = 16384: 30 us with a cospi per node, 11 us with mirrored nodes and turned angles; TERMS (the
-// reduced forms, dct2_terms) 28 -> 21 us.
+// M = 16384: 30 us with a cospi per node, 8.6 us with mirrored nodes and turned angles; TERMS (the
+// reduced forms) 28 -> 21 us.
 template <bool TERMS>
 __global__ void __launch_bounds__(256)
 k_dct2(int64_t M, const double* __restrict__ f, double* __restrict__ c, int order, int damping) {
     __shared__ double smem[4];
     const int64_t n = blockIdx.x;
-    const double acc = block_sum<256>(TERMS ? dct2_terms(n, M, f) : dct2_turned(n, M, f), smem);
+    const double acc = block_sum<256>(dct2<TERMS>(n, M, f), smem);
     if (threadIdx.x == 0) c[n] = (n == 0 ? 1.0 : 2.0) * acc / (double)M * damping_factor(damping, (int)n, order);
 }
 
@@ -188,7 +188,7 @@ k_assemble_moments(const double* __restrict__ tr_baby, const double* __restrict_
 }
 
 // w_j = sum_n (2 - delta_{n0}) tau_n cos(n theta_j) at the nodes j and M-1-j; also stores x_j.  Order 512,
-// M = 16384: 33 us with a cospi per node and term, 13 us with mirrored nodes and turned angles; TERMS
+// M = 16384: 33 us with a cospi per node and term, 11 us with mirrored nodes and turned angles; TERMS
 // 31 -> 28 us.
 template <bool TERMS>
 __global__ void __launch_bounds__(256)
@@ -370,6 +370,7 @@ hipError_t launch_fermi_coeffs(int order, int M, const DevScalars* s, double* f_
                                hipStream_t st, int damping, int terms) {
     hipLaunchKernelGGL(k_fermi_table, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st,
                        (int64_t)M, s, f_tab);
+    if (!turns_exact(M)) terms = 1;
     hipLaunchKernelGGL(terms ? k_dct2<true> : k_dct2<false>, dim3((unsigned)(order + 1)), dim3(256), 0, st, (int64_t)M,
                        (const double*)f_tab, c_out, order, damping);
     return hipGetLastError();
@@ -393,6 +394,7 @@ hipError_t launch_assemble_moments(const double* tr_baby, const double* gram, in
 hipError_t launch_dct3(const double* tau, int order, int M, double* w, double* x_tab,
                        hipStream_t st, int damping, int terms) {
     const int64_t threads = ((int64_t)M + 1) / 2 * kDctSplit;
+    if (!turns_exact(M)) terms = 1;
     hipLaunchKernelGGL(terms ? k_dct3<true> : k_dct3<false>, dim3((unsigned)((threads + 255) / 256)), dim3(256),
                        sizeof(double) * (size_t)dct3_padded(order), st, tau, order, (int64_t)M, w, x_tab, damping);
     return hipGetLastError();
