@@ -27,7 +27,8 @@ if ROOT not in sys.path:
 METRIC = "density matrices/s and % MFMA peak at N=1000/4000 vs plain FP64 path"
 PEAK_TFLOPS = {"fp64": 78.6, "fp32": 157.3, "bf16x3": 2500.0, "bf16x6": 2500.0}   # dense MFMA peaks of MI355X
 PEAK_HBM_GBS = 8000.0
-INT8_MODULI, INT8_MIN_N, PEAK_INT8_TOPS = 15, 1400, 5000.0   # float64 products on the int8 units (csrc/k_rns.hip)
+# float64 products on the int8 units (csrc/k_rns.hip): launches of several from n = MIXED_MIN_N, all from INT8_MIN_N
+INT8_MODULI, MIXED_MIN_N, INT8_MIN_N, PEAK_INT8_TOPS = 15, 960, 1400, 5000.0
 SEEDS = {1000: 2000, 2000: 2001, 4000: 2002}   # gaussmix6 workloads at order 512
 ALL_SECTIONS = ("breakdown", "fixed", "config", "lanczos", "accuracy", "diag", "batch", "learned")
 
@@ -158,8 +159,13 @@ def gemm_sources_sha256():
 
 
 def on_int8(prec, n):
-    """Whether all products of a float64 call run on the int8 units (csrc/api.hip: from n = 1400)."""
+    """Whether all products of a float64 call run on the int8 units (csrc/api.hip: dense H from n = 1400)."""
     return prec == "fp64" and n is not None and n >= INT8_MIN_N
+
+
+def on_both_units(prec, n):
+    """Whether a float64 call may launch products on either units; the profile does not tell them apart."""
+    return prec == "fp64" and n is not None and MIXED_MIN_N <= n < INT8_MIN_N
 
 
 def traffic_of(prec, n, order):
@@ -198,19 +204,21 @@ def roofline_of(prof, prec, n=None):
 
     Float64 products on the int8 units count as their INT8_MODULI int8 products against the int8
     peak (scale, split and join launches are in the time); ``f64_equivalent`` is the rate in
-    float64 flops.
+    float64 flops.  Where a call uses both units there is no one peak, and no fraction of it.
     """
     if prof["gemm_ms"] <= 0:
         return None
+    both = on_both_units(prec, n)
     int8 = on_int8(prec, n)
     # bf16 products per split product, int8 products per float64 product
     flop = prof["gemm_flop"] * (INT8_MODULI if int8 else {"bf16x3": 3.0, "bf16x6": 6.0}.get(prec, 1.0))
     achieved = flop / (prof["gemm_ms"] * 1e-3) / 1e12
-    peak = PEAK_INT8_TOPS if int8 else PEAK_TFLOPS[prec]
+    peak = None if both else PEAK_INT8_TOPS if int8 else PEAK_TFLOPS[prec]
     extra = {"f64_equivalent": round(achieved / INT8_MODULI, 3)} if int8 else {}
     return {"bound": "mfma", "achieved": round(achieved, 3), "peak": peak, "unit": "TOP/s" if int8 else "TFLOP/s",
-            "frac": round(achieved / peak, 4), "traffic": None, **extra,
-            "kernel": "k_rns_gemm (int8 products by residue arithmetic, with scale, split and join)" if int8
+            "frac": round(achieved / peak, 4) if peak else None, "traffic": None, **extra,
+            "kernel": "products on the float64 and the int8 units" if both
+                      else "k_rns_gemm (int8 products by residue arithmetic, with scale, split and join)" if int8
                       else "k_gemm (symmetric product, fused epilogue)",
             "launches": prof["gemm_launches"], "products": prof["gemm_products"],
             "avg_launch_ms": round(prof["gemm_ms"] / max(1, prof["gemm_launches"]), 4)}
