@@ -220,7 +220,7 @@ bool rns_pays(int64_t n) { return n >= kRnsMinN && (n <= 1024 || n > 1056); }
 
 // slots == 0: float64 units.  The operand sets take at most 8 GiB (12 sets up to N = 6600; below
 // three, from N = 13761, the products would convert operands over and over, and the float64 units stay).
-constexpr int kRnsMinSlots = 3, kRnsMaxSlots = 12;
+constexpr int kRnsMinSlots = 3;
 RnsLayout rns_layout(const Plan& pl) {
     RnsLayout l{};
     if (pl.prec != CHEBDM_FP64 || !rns_pays(pl.n)) return l;
@@ -228,7 +228,7 @@ RnsLayout rns_layout(const Plan& pl) {
     l.set_stride = l.geo.set_bytes + 2 * l.geo.rows * (int64_t)sizeof(double);
     const int64_t fit = ((int64_t)8 << 30) / l.set_stride;
     if (fit < kRnsMinSlots) return l;
-    l.slots = (int)std::min<int64_t>(fit, kRnsMaxSlots);
+    l.slots = (int)std::min<int64_t>(fit, kRnsSlots);
     l.products = std::max<int64_t>(1, std::min<int64_t>(kRnsGroup, ((int64_t)256 << 20) / l.geo.res_bytes));
     return l;
 }
@@ -277,8 +277,8 @@ double* rns_scale(chebdm_handle h, int s) { return reinterpret_cast<double*>(rns
 
 // No slot holds a current matrix (a new call's matrices are about to be written).
 void rns_reset(chebdm_handle h) {
-    h->rns_owner.assign(h->rns_slots, nullptr);
-    h->rns_used.assign(h->rns_slots, 0);
+    std::fill_n(h->rns_owner, kRnsSlots, nullptr);
+    std::fill_n(h->rns_used, kRnsSlots, 0);
     h->rns_clock = 0;
 }
 

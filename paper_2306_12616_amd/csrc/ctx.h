@@ -58,8 +58,8 @@ struct chebdm_ctx {
     chebdm::RnsGeom rns_geo{};
     int rns_slots = 0;                        // 0: products run on the float64 units
     int64_t rns_res_products = 0;
-    std::vector<const void*> rns_owner;       // matrix whose planes a slot holds
-    std::vector<int64_t> rns_used;
+    const void* rns_owner[chebdm::kRnsSlots] = {};   // matrix whose planes a slot holds
+    int64_t rns_used[chebdm::kRnsSlots] = {};
     int64_t rns_clock = 0;
     // Lanczos bounds workspace (basis, work vectors, partials, tridiagonal)
     double* lz = nullptr;

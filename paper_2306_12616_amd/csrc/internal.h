@@ -157,6 +157,7 @@ hipError_t launch_product_sum(const double* T, const double* R, int64_t stride, 
 // ---- float64 products by residue arithmetic on int8 MFMA (k_rns.hip)
 constexpr int kRnsModuli = 15;
 constexpr int kRnsGroup = 16;   // operands or products of one launch
+constexpr int kRnsSlots = 12;   // operand sets kept at most
 struct RnsGeom {                // sizes that follow from n
     int64_t n, rows;            // rows: n rounded up to the tile
     int kt;                     // K steps of 64
