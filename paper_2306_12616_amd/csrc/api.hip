@@ -561,11 +561,11 @@ struct Chain {
             RnsProduct prod[kRnsGroup];
             const double* mats[kRnsGroup];
             int8_t* planes[kRnsGroup];
-            RnsScale scale[kRnsGroup];
+            const double* scale[kRnsGroup];
             const double* smats[kRnsGroup];
             double* srow[kRnsGroup];
             int nsplit = 0, nscale = 0, np = 0;
-            auto scale_of = [&](int s, bool t) { return t && pl.unit ? RnsScale{nullptr, 0} : RnsScale{rns_scale(h, s), 1}; };
+            auto scale_of = [&](int s, bool t) -> const double* { return t && pl.unit ? nullptr : rns_scale(h, s); };
             auto operand = [&](const double* M, bool t) -> int {   // slot with M's planes, or -1: none free
                 int lru = -1;
                 for (int s = 0; s < h->rns_slots; ++s) {

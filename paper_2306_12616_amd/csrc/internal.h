@@ -119,6 +119,9 @@ hipError_t launch_bisect(const double* w, const double* x_tab, int M, DevScalars
                          double* work, hipStream_t st);
 
 // ---- block sums and Gram contractions (k_combine.hip)
+// Blocks formed on and above the diagonal start at their row's diagonal block of kUpper columns: the
+// product tiles' epilogues read no addend left of the diagonal's block of 16.
+constexpr int kUpper = 32;
 // Smaller blocks are formed whole.  Float64 calls of those sizes mirror one block (fixed mu; N = 700 791 ->
 // 768 us, 600 no change), the reduced forms' four (float32 N = 1000 1256 -> 1263 us, 2000 5491 -> 5412).
 constexpr int64_t combine_upper_min_n(size_t elem) { return elem == 8 ? 700 : 1200; }
@@ -168,14 +171,10 @@ struct RnsGeom {                // sizes that follow from n
     bool big;                   // 256 x 128 tiles (else 128 x 128)
 };
 RnsGeom rns_geom(int64_t n);
-// Powers of two of an operand's rows: (2^(57 - e), 2^e) at p[2 step row]; null p: e = 0 for all.
-struct RnsScale {
-    const double* p;
-    int64_t step;               // 1, or 0: one pair for all rows
-};
+// Row scales: the powers of two (2^(57 - e), 2^e) of row r at scale[2 r]; null: e = 0 for all.
 struct RnsProduct {             // Out = alpha A B + beta C + gamma E + delta I (C, E may be null)
     const int8_t *planes_a, *planes_b;
-    RnsScale scale_a, scale_b;
+    const double *scale_a, *scale_b;
     const double *C, *E;               // ld x ld workspace matrices
     double* Out;
     int64_t ld_out;
@@ -187,7 +186,7 @@ struct RnsProduct {             // Out = alpha A B + beta C + gamma E + delta I 
 hipError_t launch_rns_scale(const RnsGeom& g, int64_t ld, const double* const* mats, double* const* scale, int count,
                             hipStream_t st);
 hipError_t launch_rns_split(const RnsGeom& g, int64_t ld, const double* const* mats, int8_t* const* planes,
-                            const RnsScale* scale, int count, hipStream_t st);
+                            const double* const* scale, int count, hipStream_t st);
 // res: count * g.res_bytes
 hipError_t launch_rns_products(const RnsGeom& g, int64_t ld, const RnsProduct* prods, int count, int8_t* res,
                                hipStream_t st);

@@ -434,7 +434,6 @@ k_batch_cform(const double* __restrict__ c, int order, int k, int m, double* __r
 // small problem do not fill a work-group.  The last block, the chain's first operand, is mirrored by
 // k_batch_mirror.  Whole calls, float32, 128 problems of 96..1024, order 256: 25.6 -> 24.9 ms, 64 of 96..512
 // 4.13 -> 3.99, 8 of 96..256, order 64 845 -> 848 us; float64, 32 of 96..1024, order 128: 7.82 -> 7.64 ms.
-constexpr int kUpper = 32;
 template <typename T> struct BVec;
 template <> struct BVec<double> { typedef double V __attribute__((ext_vector_type(2))); static constexpr int W = 2; };
 template <> struct BVec<float> { typedef float V __attribute__((ext_vector_type(4))); static constexpr int W = 4; };

@@ -43,7 +43,6 @@ template <> struct Vec<double> { using V = f64x2; static constexpr int W = 2; };
 template <> struct Vec<float> { using V = f32x2; static constexpr int W = 2; };
 
 constexpr int kCombineThreads = 256;
-constexpr int kUpper = 32;   // the gemm tiles' epilogues read no addend left of the diagonal's block of 16
 
 template <typename T, int MB, bool UPPER>
 __global__ void __launch_bounds__(kCombineThreads)

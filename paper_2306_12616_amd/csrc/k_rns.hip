@@ -30,6 +30,7 @@
 #include <cstdint>
 
 #include "internal.h"
+#include "lds_copy.h"
 
 namespace chebdm {
 
@@ -169,7 +170,7 @@ struct ScaleArgs {
 struct SplitArgs {
     const double* A[kRnsGroup];
     int8_t* planes[kRnsGroup];
-    RnsScale scale[kRnsGroup];
+    const double* scale[kRnsGroup];
 };
 
 // One wavefront per row: the power of two above the row's 2-norm.  One pass over the matrix, bound
@@ -238,8 +239,8 @@ __global__ void __launch_bounds__(256) k_rns_split(const SplitArgs a, int64_t n,
     if (kb >= kt) return;
     const int64_t row = (int64_t)rb * 16 + lane % 16;
     const int64_t k0 = (int64_t)kb * 64 + (lane / 16) * 2;
-    const RnsScale sc = a.scale[blockIdx.z];
-    const double s = sc.p ? sc.p[2 * sc.step * row] : 0x1p57;
+    const double* scale = a.scale[blockIdx.z];
+    const double s = scale ? scale[2 * row] : 0x1p57;
     const double* A = a.A[blockIdx.z] + row * ld + k0;
     uint32_t lo[16], hi[16];
 #pragma unroll
@@ -281,12 +282,6 @@ struct GemmArgs {
     const int8_t* B[kRnsGroup];
 };
 
-// One 1 KB chunk from memory into LDS (lane l's 16 bytes at lds + 16 l), without passing registers.
-__device__ __forceinline__ void copy_chunk(uint32_t lds, uint32_t voff, const void* base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
-                 : "memory");
-}
-
 // Work-group: WM x WN wavefronts of TM x TN fragments (16 x 16), K in steps of 64, S LDS stages.
 // Step k waits for its own copies of stage k, passes the barrier (stage k is then complete and
 // everyone has read stage k - 1: its reads end before the wait), starts the copies of stage
@@ -327,7 +322,7 @@ k_rns_gemm(const GemmArgs g, int64_t plane_bytes, int kt, int ntr, int ntc, int 
     auto issue = [&](int k) {
         const uint32_t l = ldsw + (uint32_t)(k % S) * STAGE;
 #pragma unroll
-        for (int c = 0; c < CW; ++c) copy_chunk(l + c * 1024, voff + (uint32_t)k * 1024u, src[c]);
+        for (int c = 0; c < CW; ++c) copy_1k(l + c * 1024, voff + (uint32_t)k * 1024u, src[c]);
     };
     const int wm = w % WM, wn = w / WM;
     const bool live = (ti * WM + wm) * TM < (tj * WN + wn + 1) * TN;   // not wholly below the diagonal
@@ -410,7 +405,7 @@ k_rns_join(const JoinArgs jn, int64_t n, int64_t ld, int ntr, int ntc, int ntile
     r[15] = (v4i){0, 0, 0, 0};
     const int64_t j = j0 + lane % 16;
     const bool jin = j < n;
-    const double sb = !jin ? 0.0 : d.scale_b.p ? d.scale_b.p[2 * d.scale_b.step * j + 1] : 1.0;
+    const double sb = !jin ? 0.0 : d.scale_b ? d.scale_b[2 * j + 1] : 1.0;
     const bool whole = i0 + 63 < j0 && i0 + 63 < n && d.vec;   // off the diagonal, aligned rows
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -444,7 +439,7 @@ k_rns_join(const JoinArgs jn, int64_t n, int64_t ld, int ntr, int ntc, int ntile
             const int64_t i = ib + x;
             o[x] = 0.0;
             if (i < n && jin) {
-                const double sa = d.scale_a.p ? d.scale_a.p[2 * d.scale_a.step * i + 1] : 1.0;
+                const double sa = d.scale_a ? d.scale_a[2 * i + 1] : 1.0;
                 double v = d.alpha * (fma(f, kTab.p_hi, f * kTab.p_lo) * sa * sb);
                 if (d.C) v = fma(d.beta, d.C[i * ld + j], v);
                 if (d.E) v = fma(d.gamma, d.E[i * ld + j], v);
@@ -512,7 +507,7 @@ hipError_t launch_rns_scale(const RnsGeom& g, int64_t ld, const double* const* m
 }
 
 hipError_t launch_rns_split(const RnsGeom& g, int64_t ld, const double* const* mats, int8_t* const* planes,
-                            const RnsScale* scale, int count, hipStream_t st) {
+                            const double* const* scale, int count, hipStream_t st) {
     if (count < 1 || count > kRnsGroup || ld < g.n || ld % 2 != 0) return hipErrorInvalidValue;
     SplitArgs a{};
     for (int i = 0; i < count; ++i) {

@@ -11,6 +11,7 @@
 // XCD then reads its own eighth of the matrices instead of all of them.  Operands are symmetric and read
 // along rows as in k_gemm.hip, two register stages.
 #include "internal.h"
+#include "lds_copy.h"
 
 namespace chebdm {
 
@@ -173,12 +174,6 @@ hipError_t launch(const double* T, const double* R, int64_t stride, int prods, c
 constexpr int kBig = 96, kHalf = 48, kStages = 3, kCopies = 6;
 constexpr int kPart = kBig * kBig;              // doubles of a piece: wavefront, 36 registers, lane
 constexpr int kStageBytes = 4 * kCopies * 1024;
-
-// 16 bytes a lane from base + voff into LDS at lds + 16 lane, without passing registers.
-__device__ __forceinline__ void copy_1k(uint32_t lds, uint32_t voff, const void* base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
-                 : "memory");
-}
 
 struct Ranges {   // of one XCD
     int64_t first, units, total;   // first unit, units of a tile, tiles times units
