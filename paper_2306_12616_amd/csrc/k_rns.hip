@@ -289,7 +289,7 @@ struct GemmArgs {
 // LDS reads are 16 contiguous bytes a lane: no bank conflicts.  A wavefront whose block lies below
 // the diagonal copies for the others and multiplies nothing (the join never reads its residues).
 // Bound by the power of the matrix units and by LDS and copy traffic together (N = 4000, one product,
-// int8 rate executed: 2.29 POP/s with 128 x 128 tiles, three work-groups a CU; the vendor library's
+// int8 rate executed: 2.29 POP/s with 128 x 128 tiles, three work-groups a CU, 2.39 with these; the vendor library's
 // int8 GEMM at 4096: 2.08; the 128-tile loop without copies 3.3, without LDS reads too 3.6; zero
 // operands alone, which switch less, gave 16 %).  The wavefront's 64 x 128 block, against 64 x 64, reads
 // a quarter less LDS per product.  mu search and D of order 512, N = 2000 / 2500 / 3000 / 4000 / 4600:
