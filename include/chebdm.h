@@ -71,8 +71,8 @@ enum chebdm_prec {
 
 /* Fixed-point products lose the digits of entries far below their row, so they are taken only for an H
  * with (sum |h_ij|)^2 > (n - 1)/2 sum h_ij^2 over j != i in every row i (normal entries have 2/pi in place
- * of the 1/2; a weakly coupled fragment, a band or a decaying row is below it) and sum |h_ij| at least an
- * eighth of emax - emin.  The call looks while it waits for the device: always with bounds of its own, with
+ * of the 1/2; a weakly coupled fragment, a band or a decaying row is below it) and sum |h_ij| at least a
+ * third of emax - emin.  The call looks while it waits for the device: always with bounds of its own, with
  * given ones unless it is chebdm_density without info.  Other calls, and calls without the memory for the
  * residue planes, take the float64 units; both are deterministic, their last digits differ. */
 

@@ -410,15 +410,17 @@ int lanczos_on_device(chebdm_handle h, const double* dH, int64_t n, int64_t ldh,
 // and entries below 2^-58 become zero.  So the rows of H have to be spread out: with
 // (sum |h|)^2 > c (n - 1) sum h^2 off the diagonal in every row, each row is within acos(sqrt(c)) of the
 // all-ones direction and sum_k |h_ik h_jk| > (2 c - 1) |h_i| |h_j| for any two; c = 1/2 is where two
-// rows could be apart.  Normal entries have 2/pi (at least 0.59 over n = 960 .. 5000 dense test matrices of
-// three spectra), two uncoupled halves 1/pi, a band of b entries b / n.  And the radius of every row
-// has to be a fair part of the half-width that scales it (0.80 to 0.93 of Gershgorin's, about 10 of the
-// spectrum's): a row that is nearly all diagonal has its other entries far below the scale.
+// rows could be apart.  Normal entries have 2/pi (at least 0.59 in dense test matrices of three spectra,
+// n = 960 .. 4000), two uncoupled halves 1/pi, a band of b entries b / n.  And the radius of every row
+// has to be two thirds of the half-width that scales it (0.80 to 0.93 of Gershgorin's in those matrices, about
+// 10 of the spectrum's): where the diagonal takes its share of the width the other entries lie further below
+// the scale.  Error off the diagonal, order 64, n = 1000 .. 2000, of the float64 units': radius at 0.26 2.2 to 2.4,
+// at 0.69 0.7 to 0.9; two halves coupled by 0.55 (spread 0.55) 0.75 to 1.0, in their coupling block 1.2.
 // For such H the largest error of D is 0.1 to 1.06 of the float64 units' (n = 960 .. 3000, orders 64 .. 1200,
 // either bounds), its root mean square off the diagonal 0.25 to 1.01.  The sums come with Gershgorin's pass
 // over H.
 bool dense_rows(const DevScalars& s, double emin, double emax) {
-    return s.spread > 0.5 && s.radius >= 0.25 * (0.5 * (emax - emin));
+    return s.spread > 0.5 && 3.0 * s.radius >= emax - emin;
 }
 
 // Bounds: the caller's, or computed here (one read-back): Gershgorin's, then with
